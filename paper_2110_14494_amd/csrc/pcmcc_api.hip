@@ -61,7 +61,6 @@ int pcmcc_destroy(pcmcc_ctx* c) {
   dfree(c->dC);
   dfree(c->dP);
   dfree(c->dNu);
-  dfree(c->partial);
   dfree(c->ctl);
   dfree(c->fbound);
   dfree(c->fpack);

@@ -110,7 +110,7 @@ int pcmcc_streamer_steps(pcmcc_ctx* c, const pcmcc_particles* p, const pcmcc_gri
   ev.ax = e + 4 * ec; ev.ay = e + 5 * ec; ev.az = e + 6 * ec; ev.aw = e + 7 * ec;
   ev.n = c->sc_red + 5;
   ev.cap = c->ev_cap;
-  ev.overflow = &c->ctl->overflow;
+  ev.overflow = &c->ctl->overflow.v;
   pcmcc_grid cur = *applied;
   cur.E = (const float*)c->sc_E;
   const double gas_N = c->gas_N;

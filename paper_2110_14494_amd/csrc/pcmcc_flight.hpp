@@ -422,7 +422,11 @@ __device__ __forceinline__ int flight_complete(Flight& f, const double3 an, cons
 // (tables of ROW floats per node, table_row(nproc)),
 // REFILL lanes at a time (see above), `chunk` (a power of two in [kChunkMin,
 // kChunkMax], read from the kernel arguments) electrons per work-counter
-// grab, or with GUIDED a shrinking share of the rest down to kChunkMin.
+// grab, or with GUIDED a shrinking share of the rest down to kChunkMin.  A
+// wave's first chunk is its own by position (no atomic): with the work
+// counter's same-address atomics, 13 ns each, 4096 waves would need 55 us
+// just to find out what there is to do, which is all that a newborn
+// generation of a few thousand electrons takes.
 // Field: key(tag) gives the random-number key of a group, accel(x, y, z,
 // tag, where) the acceleration (and where the field was read), bound_at(where,
 // tag, speed, t_rem, a_abs, da) the field bounds for the rest of the step.
@@ -436,8 +440,8 @@ __device__ __forceinline__ int flight_complete(Flight& f, const double3 an, cons
 // staged results; can_open() tells whether the wave may take another chunk
 // of work, open_chunk(first, size) registers a chunk it took and returns its
 // tag, which tag(Flight&, tag) gives each electron loaded from it.  Must be called by whole waves with wave-uniform
-// arguments; `take` is the grid-wide work counter (zero before the first
-// wave starts).  cum_ion (nullable) counts ionizations per group.  Every
+// arguments; `take` is the grid-wide work counter beyond the first chunks
+// (zero before the first wave starts).  cum_ion (nullable) counts ionizations per group.  Every
 // staged entry is written out before the function returns.
 template <int REFILL, int ROW, bool GUIDED, class Field, class Source, class Finish>
 __device__ __forceinline__ void fly_all(uint64_t n, unsigned long long* take, KArg<uint32_t> chunk, double dt,
@@ -449,11 +453,30 @@ __device__ __forceinline__ void fly_all(uint64_t n, unsigned long long* take, KA
   StagedBirths<Field> births{L, sink, F, step, S, cum_ion, 0u};
   uint32_t n_done = 0;  // entries of the finish list
   uint64_t pool_next = 0, pool_end = 0;
-  uint64_t seen = 0;  // the work counter after this wave's previous grab
   uint32_t chunk_tag = 0;  // finisher's tag of the current chunk
   uint32_t src_hint = 0;   // source's hint for the current chunk
-  bool dry = n == 0;
   const uint32_t lane = lane_id();
+  // First chunks: one per wave, wave w of block b at place w gridDim + b, so
+  // that a short phase spreads over the blocks; half of an even share of the
+  // work, between kChunkMin and the schedule's chunk (a phase that fits one
+  // kChunkMin per wave needs no work counter at all).
+  const uint32_t waves = gridDim.x * (blockDim.x >> 6);
+  uint64_t first;  // electrons in all first chunks together
+  {
+    const uint64_t share = n / (2u * (uint64_t)waves);
+    const uint32_t most = chunk.get();
+    const uint32_t ch = share < (uint64_t)kChunkMin ? kChunkMin : (share < (uint64_t)most ? (uint32_t)share : most);
+    const uint32_t w = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) * gridDim.x + blockIdx.x);
+    first = (uint64_t)ch * waves;
+    pool_next = (uint64_t)ch * w;
+    pool_end = pool_next + ch < n ? pool_next + ch : n;
+  }
+  bool dry = pool_next >= n;
+  if (!dry) {
+    chunk_tag = finish.open_chunk(pool_next, (uint32_t)(pool_end - pool_next));
+    src_hint = source.hint(pool_next);
+  }
+  uint64_t seen = first;  // the work taken as of this wave's previous grab
   for (;;) {
     const uint64_t busy = __ballot(f.mode == FM_FLY);
     if (64u - (uint32_t)__popcll(busy) >= (uint32_t)REFILL || busy == 0) {
@@ -479,6 +502,10 @@ __device__ __forceinline__ void fly_all(uint64_t n, unsigned long long* take, KA
         uint32_t served = 0;
         while (served < n_idle) {
           if (pool_next == pool_end) {
+            if (seen >= n) {
+              dry = true;
+              break;
+            }
             if (!finish.can_open()) break;  // the lanes stay idle until a chunk of this wave completes
             // GUIDED: a share of what was left at this wave's previous grab,
             // (n - seen) / (2 waves), between kChunkMin and the schedule's
@@ -487,16 +514,15 @@ __device__ __forceinline__ void fly_all(uint64_t n, unsigned long long* take, KA
             // 1 % on its large phases; the swarms' short steps lose more to
             // the extra grabs than they gain).
             uint32_t ch = chunk.get();
-            if (GUIDED && seen > 0) {
-              const uint64_t waves = (uint64_t)gridDim.x * blockDim.x / 64u;
-              const uint64_t share = seen < n ? (n - seen) / (2u * waves) : 0u;
+            if (GUIDED) {
+              const uint64_t share = (n - seen) / (2u * (uint64_t)waves);
               ch = share < (uint64_t)kChunkMin ? (uint32_t)kChunkMin : (share < ch ? (uint32_t)share : ch);
             }
             unsigned long long base = 0;
             if (lane == 0) base = atomicAdd(take, (unsigned long long)ch);
             const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)base);
             const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(base >> 32));
-            const uint64_t b = ((uint64_t)hi << 32) | lo;
+            const uint64_t b = first + (((uint64_t)hi << 32) | lo);
             seen = b + ch;
             if (b >= n) {
               dry = true;

@@ -6,6 +6,7 @@
 
 #include "pcmcc.h"
 #include "pcmcc_device.hpp"
+#include "pcmcc_gridsync.hpp"
 
 namespace pcmcc {
 
@@ -52,22 +53,34 @@ struct EventSink {
 // weights and resumes).
 constexpr int kStatusWeightsDue = 1;
 
-// Device control block of a step loop.
+// A counter on a cache line of its own: every wave of the grid adds to these,
+// and same-line atomics are served one after the other.
+template <class T>
+struct alignas(128) OnLine {
+  T v;
+};
+using CtlLine = OnLine<unsigned long long>;
+
+// Device control block of a step loop (uploaded by the host before every
+// launch, with the barrier state zero).  A step's phases are numbered from 0
+// (the current buffer), then one per newborn generation; phase p takes work
+// from take[p & 1] and generation g = p - 1 reads the queue counted by
+// pend[g & 1] and fills the other one.
 struct Ctl {
-  unsigned long long n_cur;   // live particles in the current buffer
-  unsigned long long holes;   // removed particles of this step (slots in the next buffer)
-  unsigned long long child;   // newborn survivors placed so far
-  unsigned long long donors;  // tail donors found (hole filling)
-  unsigned long long fill;    // holes filled from the tail
-  unsigned long long pend[kMaxGenerations + 1];  // newborns queued per generation
-  unsigned long long take[kMaxGenerations + 1];  // work counters: current buffer, then each generation
-  unsigned overflow;          // Overflow bits of the running step
-  int cur_sel;                // 0: the caller's arrays are current, 1: the scratch buffer
-  int stop;
-  int status;
-  long long steps_done;
+  CtlLine holes;    // removed particles of this step (slots in the next buffer)
+  CtlLine child;    // newborn survivors placed so far
+  CtlLine donors;   // tail donors found (hole filling)
+  CtlLine fill;     // holes filled from the tail
+  CtlLine pend[2];  // newborns queued
+  CtlLine take[2];  // work counters
+  OnLine<unsigned> overflow;  // Overflow bits of the running step
+  GridBar bar;
+  unsigned long long n_cur;  // live particles in the current buffer
   unsigned long long particle_steps;
-  unsigned long long tot[NCNT];
+  long long steps_done;
+  int cur_sel;  // 0: the caller's arrays are current, 1: the scratch buffer
+  int status;
+  CtlLine tot[NCNT];
 };
 
 // Schedule choices of the mover (chosen per workload by the launch-shape
@@ -82,7 +95,6 @@ struct PicArgs {
   uint32_t* holes;
   uint32_t* flags;
   uint32_t* donor;
-  unsigned long long* partial;  // [grid][NCNT]
   uint64_t cap, pend_cap;
   Ctl* ctl;
   const unsigned* emax_bits;  // max |E| over the cells, as float bits

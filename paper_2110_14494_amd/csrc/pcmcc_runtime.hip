@@ -472,12 +472,6 @@ int push_impl(pcmcc_ctx* c, const pcmcc_particles* p, const pcmcc_grid* field, d
   rc = resolve_launch(c, c->sched, pic_lds_bytes_s, occupancy_pic_steps, T, 0, &sl, (uint64_t)std::max<int64_t>(n0, 1));
   if (rc) return rc;
   const int block = sl.block, grid = sl.grid;
-  if (c->partial_blocks < grid) {
-    dfree(c->partial);
-    c->partial = nullptr;
-    HIP_TRY(c, dalloc(&c->partial, (size_t)grid * NCNT));
-    c->partial_blocks = grid;
-  }
   std::memset(c->host_ctl, 0, sizeof(Ctl));
   c->host_ctl->n_cur = (unsigned long long)n0;
   // The steps alternate between the caller's arrays and the scratch buffer.
@@ -524,7 +518,6 @@ int push_impl(pcmcc_ctx* c, const pcmcc_particles* p, const pcmcc_grid* field, d
   A.holes = c->holes;
   A.flags = c->flags;
   A.donor = c->donor;
-  A.partial = c->partial;
   A.cap = (uint64_t)p->capacity;
   A.pend_cap = c->pend_cap;
   A.ctl = c->ctl;
@@ -592,7 +585,7 @@ int push_impl(pcmcc_ctx* c, const pcmcc_particles* p, const pcmcc_grid* field, d
                                   (uint64_t)p->capacity, &n_new, &pairs, &splits);
     HIP_TRY(c, hipEventRecord(c->ev[3], c->stream));
     h.status = PCMCC_OK;
-    h.stop = 0;
+    std::memset(&h.bar, 0, sizeof(h.bar));
     if (urc == PCMCC_OK) {
       HIP_TRY(c, hipStreamSynchronize(c->stream));
       HIP_TRY(c, hipEventElapsedTime(&ms, c->ev[2], c->ev[3]));
@@ -636,13 +629,13 @@ int push_impl(pcmcc_ctx* c, const pcmcc_particles* p, const pcmcc_grid* field, d
     stats->n = (int64_t)h.n_cur;
     stats->steps_done = h.steps_done;
     stats->particle_steps = h.particle_steps;
-    stats->trials = h.tot[C_TRIALS];
-    stats->null_collisions = h.tot[C_NULL];
-    for (int k = 0; k < 4; ++k) stats->real_collisions[k] = h.tot[C_EL + k];
-    stats->lost = h.tot[C_LOST];
-    stats->out_of_table = h.tot[C_OOT];
-    stats->errors = h.tot[C_ERR];
-    stats->majorant_violations = h.tot[C_MAJ];
+    stats->trials = h.tot[C_TRIALS].v;
+    stats->null_collisions = h.tot[C_NULL].v;
+    for (int k = 0; k < 4; ++k) stats->real_collisions[k] = h.tot[C_EL + k].v;
+    stats->lost = h.tot[C_LOST].v;
+    stats->out_of_table = h.tot[C_OOT].v;
+    stats->errors = h.tot[C_ERR].v;
+    stats->majorant_violations = h.tot[C_MAJ].v;
     stats->weight_updates = (int64_t)w_updates;
     stats->merged_pairs = (int64_t)w_pairs;
     stats->splits = (int64_t)w_splits;

@@ -46,8 +46,6 @@ struct pcmcc_ctx {
   Soa scratch{};
   PendSoa pend[2]{};
   uint32_t *holes = nullptr, *flags = nullptr, *donor = nullptr;
-  unsigned long long* partial = nullptr;
-  int partial_blocks = 0;
   Ctl* ctl = nullptr;
   Ctl* host_ctl = nullptr;  // pinned
   float2* fbound = nullptr;
