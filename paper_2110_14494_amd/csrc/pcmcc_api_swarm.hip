@@ -11,15 +11,14 @@ namespace {
 int swarm_run(pcmcc_ctx* c, SwarmArgs& A, int S, const std::vector<uint64_t>& n0h, const StepLaunch& L, float* ms) {
   A.chunk = (uint32_t)L.chunk;
   auto& w = c->sw;
-  HIP_TRY(c, hipMemsetAsync(w.n_nxt, 0, sizeof(unsigned long long) * S, c->stream));
+  HIP_TRY(c, hipMemsetAsync(w.n3, 0, sizeof(unsigned long long) * 3 * S, c->stream));
   HIP_TRY(c, hipMemsetAsync(w.cum_ion, 0, sizeof(unsigned long long) * S, c->stream));
   HIP_TRY(c, hipMemsetAsync(w.cum_att, 0, sizeof(unsigned long long) * S, c->stream));
-  HIP_TRY(c, hipMemsetAsync(w.pc_k, 0, sizeof(int) * S, c->stream));
   HIP_TRY(c, hipMemsetAsync(w.L, 0, sizeof(long long) * S, c->stream));
   HIP_TRY(c, hipMemsetAsync(w.mom, 0, sizeof(unsigned long long) * S * A.n_samples * kNMom * 2, c->stream));
   HIP_TRY(c, hipMemsetAsync(w.cnt, 0, sizeof(long long) * S * A.n_samples * 4, c->stream));
   HIP_TRY(c, hipMemsetAsync(w.ctl, 0, sizeof(SwarmCtl), c->stream));
-  HIP_TRY(c, hipMemcpyAsync(w.n_cur, n0h.data(), sizeof(uint64_t) * S, hipMemcpyHostToDevice, c->stream));
+  HIP_TRY(c, hipMemcpyAsync(w.n3, n0h.data(), sizeof(uint64_t) * S, hipMemcpyHostToDevice, c->stream));
   HIP_TRY(c, launch_swarm_init(w.buf[0], w.base, w.n0, S, c->stream));
   HIP_TRY(c, hipEventRecord(c->ev[0], c->stream));
   HIP_TRY(c, launch_swarm_steps(A, L.grid, L.block, L.refill, c->stream));
@@ -84,8 +83,7 @@ int pcmcc_swarm_batch(pcmcc_ctx* c, int n_swarms, const double* EN_Td, const int
   auto resolve = [&](const pcmcc_schedule& s, StepLaunch* L) {
     return resolve_launch(c, s, swarm_lds_bytes_s, occupancy_swarm_steps, T, S, L);
   };
-  const int max_grid = 32 * c->num_cu;
-  rc = ensure_swarm(c, S, slots, J, max_grid);
+  rc = ensure_swarm(c, S, slots, J);
   if (rc) return rc;
   auto& w = c->sw;
   HIP_TRY(c, hipMemcpyAsync(w.base, base.data(), sizeof(uint64_t) * S, hipMemcpyHostToDevice, c->stream));
@@ -105,16 +103,12 @@ int pcmcc_swarm_batch(pcmcc_ctx* c, int n_swarms, const double* EN_Td, const int
   A.n0 = w.n0;
   A.az = w.az;
   A.ctl = w.ctl;
-  A.n_cur = w.n_cur;
-  A.n_nxt = w.n_nxt;
-  A.pc_k = w.pc_k;
+  A.n3 = w.n3;
   A.L = w.L;
   A.cum_ion = w.cum_ion;
   A.cum_att = w.cum_att;
   A.mom = w.mom;
   A.cnt_out = w.cnt;
-  A.partial = w.partial;
-  A.partial_ps = w.partial_ps;
   A.T = T;
   A.S = species_view(c);
   A.key = Key{(uint32_t)seed, (uint32_t)(seed >> 32)};
@@ -207,13 +201,13 @@ int pcmcc_swarm_batch(pcmcc_ctx* c, int n_swarms, const double* EN_Td, const int
   }
   if (stats) {
     stats->steps_done = hc.steps_done;
-    stats->particle_steps = hc.particle_steps;
-    stats->trials = hc.tot[C_TRIALS];
-    stats->null_collisions = hc.tot[C_NULL];
-    for (int k = 0; k < 4; ++k) stats->real_collisions[k] = hc.tot[C_EL + k];
-    stats->out_of_table = hc.tot[C_OOT];
-    stats->errors = hc.tot[C_ERR];
-    stats->majorant_violations = hc.tot[C_MAJ];
+    stats->particle_steps = hc.tot[NCNT].v;
+    stats->trials = hc.tot[C_TRIALS].v;
+    stats->null_collisions = hc.tot[C_NULL].v;
+    for (int k = 0; k < 4; ++k) stats->real_collisions[k] = hc.tot[C_EL + k].v;
+    stats->out_of_table = hc.tot[C_OOT].v;
+    stats->errors = hc.tot[C_ERR].v;
+    stats->majorant_violations = hc.tot[C_MAJ].v;
     stats->step_kernel_ms = ms;
     stats->launch_block = block;
     stats->launch_grid = grid;

@@ -172,17 +172,16 @@ enum Quantity {
   Q_NU_ATT, Q_NU_EFF, Q_MEAN_EPS, Q_MU, Q_ALPHA, Q_ETA, Q_RATIO, kNQ
 };
 
-// Device control block of the swarm step loop.
+// Device control block of the swarm step loop (zero at the start; the phases
+// of a step use pend and take as in Ctl).
 struct SwarmCtl {
-  unsigned long long pend[kMaxGenerations + 1];
-  unsigned long long take[kMaxGenerations + 1];  // work counters: current buffers, then each generation
-  unsigned overflow;
-  int cur_sel;
-  int stop;
-  int status;
+  CtlLine pend[2];
+  CtlLine take[2];
+  OnLine<unsigned> overflow;
+  GridBar bar;
   long long steps_done;
-  unsigned long long particle_steps;
-  unsigned long long tot[NCNT];
+  int status;
+  CtlLine tot[NCNT + 1];  // the event counters, then the particle-steps
 };
 
 struct SwarmArgs {
@@ -195,16 +194,13 @@ struct SwarmArgs {
   const int32_t* n0;            // [S]
   const double* az;             // [S] acceleration along z
   SwarmCtl* ctl;
-  unsigned long long* n_cur;    // [S]
-  unsigned long long* n_nxt;    // [S]
-  int* pc_k;                    // [S] population control for the next load
-  long long* L;                 // [S] log2 of the weight scale
+  unsigned long long* n3;       // [3][S] electrons per swarm: step st reads row st % 3, counts its survivors in the
+                                // next row and clears the one after
+  long long* L;                 // [S] log2 of the weight scale (block 0's)
   unsigned long long* cum_ion;  // [S]
   unsigned long long* cum_att;  // [S]
   unsigned long long* mom;      // [S][J][kNMom][2] 128-bit sums (lo, hi)
   long long* cnt_out;           // [S][J][4]: count, L, ionizations, attachments
-  unsigned long long* partial;  // [grid][NCNT]
-  unsigned long long* partial_ps;  // [grid]
   TableView T;
   SpeciesView S;
   Key key;

@@ -330,7 +330,7 @@ template <int REFILL, int ROW>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k_pic_steps(PicArgs A) {
   extern __shared__ float smem[];
   __shared__ uint32_t s_pub[kBarWords];
-  __shared__ unsigned long long s_tot[8][NCNT];  // counters of the committed steps, per wave
+  __shared__ unsigned long long s_tot[NCNT];  // counters of the committed steps
   const Tab T = stage_tables(A.T, A.S, smem);
   WaveStage* L = reinterpret_cast<WaveStage*>(smem + pic_stage_offset_floats(A.T)) + (threadIdx.x >> 6);
   ChunkRing* ring = reinterpret_cast<ChunkRing*>(reinterpret_cast<WaveStage*>(smem + pic_stage_offset_floats(A.T)) +
@@ -341,7 +341,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
   const auto* ka = (const __attribute__((address_space(4))) PicArgs*)__builtin_amdgcn_kernarg_segment_ptr();
   const GridField F{G, A.S.qm, A.key, &ka->G};
   Ctl* ctl = A.ctl;
-  if (lane_id() < NCNT) s_tot[threadIdx.x >> 6][lane_id()] = 0ull;
+  if (threadIdx.x < NCNT) s_tot[threadIdx.x] = 0ull;  // first added to after a barrier
   uint32_t gen = 0;  // barriers so far
   auto none = [](uint32_t*) {};
   // words of the last barrier, wave-uniform
@@ -422,18 +422,14 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
 #pragma unroll
     for (int k = 0; k < NCNT; ++k) {
       const uint32_t t = wave_sum_dpp(cnt.v[k]);
-      if (lane_id() == 0) s_tot[threadIdx.x >> 6][k] += t;
+      if (lane_id() == 0) atomicAdd(&s_tot[k], (unsigned long long)t);
     }
     if (code == STEP_LAST) break;
     n_cur = word(4);
     sel ^= 1;
   }
   __syncthreads();
-  if (threadIdx.x < NCNT) {
-    unsigned long long t = 0;
-    for (unsigned w = 0; w < (blockDim.x >> 6); ++w) t += s_tot[w][threadIdx.x];
-    if (t) atomicAdd(&ctl->tot[threadIdx.x].v, t);
-  }
+  if (threadIdx.x < NCNT && s_tot[threadIdx.x]) atomicAdd(&ctl->tot[threadIdx.x].v, s_tot[threadIdx.x]);
 }
 
 // Copies the final state back to the caller's arrays if it ended in the

@@ -16,11 +16,6 @@ namespace pcmcc {
 // ---------------------------------------------------------------------------
 // small device helpers
 
-template <class T>
-__device__ __forceinline__ T ld_acq(const T* p) {
-  return __hip_atomic_load(p, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 __device__ __forceinline__ unsigned lane_id() { return __lane_id(); }
 
 __device__ __forceinline__ uint32_t rank_in(uint64_t mask) {
@@ -374,21 +369,5 @@ __device__ inline Tab stage_tables(const TableView& TV, const SpeciesView& S, fl
   T.eps_max = TV.eps_top;
   return T;
 }
-
-// Sums per-thread counters over the block into partial[blockIdx.x][*].
-__device__ inline void block_counters(const Cnt& c, unsigned long long* partial) {
-  __shared__ unsigned long long red[NCNT];
-  if (threadIdx.x < NCNT) red[threadIdx.x] = 0;
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < NCNT; ++k) {
-    uint32_t v = c.v[k];
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    if (lane_id() == 0) atomicAdd(&red[k], (unsigned long long)v);
-  }
-  __syncthreads();
-  if (threadIdx.x < NCNT) partial[(size_t)blockIdx.x * NCNT + threadIdx.x] = red[threadIdx.x];
-}
-
 
 }  // namespace pcmcc

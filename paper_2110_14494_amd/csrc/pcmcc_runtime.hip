@@ -98,8 +98,8 @@ void free_swarm(pcmcc_ctx* c) {
   auto& w = c->sw;
   for (auto& b : w.buf) free_soa(b);
   for (auto& q : w.pend) free_pend(q);
-  void* ps[] = {w.base, w.cap_s, w.n0, w.az, w.EN, w.n_cur, w.n_nxt, w.cum_ion, w.cum_att, w.pc_k, w.L,
-                w.mom, w.cnt, w.partial, w.partial_ps, w.ctl, w.values, w.errors, w.work};
+  void* ps[] = {w.base, w.cap_s, w.n0, w.az, w.EN, w.n3, w.cum_ion, w.cum_att, w.L,
+                w.mom, w.cnt, w.ctl, w.values, w.errors, w.work};
   for (void* q : ps) dfree(q);
   w = pcmcc_ctx::Swarm{};
 }
@@ -119,10 +119,10 @@ int alloc_pend(pcmcc_ctx* c, PendSoa& q, uint64_t n, bool with_sw) {
   return PCMCC_OK;
 }
 
-// Swarm scratch for S swarms, `slots` particle slots, J samples, `grid` blocks.
-int ensure_swarm(pcmcc_ctx* c, int S, uint64_t slots, int J, int grid) {
+// Swarm scratch for S swarms, `slots` particle slots, J samples.
+int ensure_swarm(pcmcc_ctx* c, int S, uint64_t slots, int J) {
   auto& w = c->sw;
-  if (w.S >= S && w.slots >= slots && w.J >= J && w.grid >= grid && w.ctl) return PCMCC_OK;
+  if (w.S >= S && w.slots >= slots && w.J >= J && w.ctl) return PCMCC_OK;
   free_swarm(c);
   int rc;
   for (auto& b : w.buf)
@@ -135,16 +135,12 @@ int ensure_swarm(pcmcc_ctx* c, int S, uint64_t slots, int J, int grid) {
   HIP_TRY(c, dalloc(&w.n0, S));
   HIP_TRY(c, dalloc(&w.az, S));
   HIP_TRY(c, dalloc(&w.EN, S));
-  HIP_TRY(c, dalloc(&w.n_cur, S));
-  HIP_TRY(c, dalloc(&w.n_nxt, S));
+  HIP_TRY(c, dalloc(&w.n3, 3 * (size_t)S));
   HIP_TRY(c, dalloc(&w.cum_ion, S));
   HIP_TRY(c, dalloc(&w.cum_att, S));
-  HIP_TRY(c, dalloc(&w.pc_k, S));
   HIP_TRY(c, dalloc(&w.L, S));
   HIP_TRY(c, dalloc(&w.mom, (size_t)S * J * kNMom * 2));
   HIP_TRY(c, dalloc(&w.cnt, (size_t)S * J * 4));
-  HIP_TRY(c, dalloc(&w.partial, (size_t)grid * NCNT));
-  HIP_TRY(c, dalloc(&w.partial_ps, (size_t)grid));
   HIP_TRY(c, dalloc(&w.ctl, 1));
   HIP_TRY(c, dalloc(&w.values, (size_t)S * kNQ));
   HIP_TRY(c, dalloc(&w.errors, (size_t)S * kNQ));
@@ -152,7 +148,6 @@ int ensure_swarm(pcmcc_ctx* c, int S, uint64_t slots, int J, int grid) {
   w.S = S;
   w.slots = slots;
   w.J = J;
-  w.grid = grid;
   w.pend_cap = pc;
   return PCMCC_OK;
 }

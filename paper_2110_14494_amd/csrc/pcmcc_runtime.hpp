@@ -102,18 +102,16 @@ struct pcmcc_ctx {
   // swarm batch scratch
   struct Swarm {
     uint64_t slots = 0, pend_cap = 0;
-    int S = 0, J = 0, grid = 0;
+    int S = 0, J = 0;
     Soa buf[2]{};
     PendSoa pend[2]{};
     uint64_t *base = nullptr, *cap_s = nullptr;
     int32_t* n0 = nullptr;
     double *az = nullptr, *EN = nullptr;
-    unsigned long long *n_cur = nullptr, *n_nxt = nullptr, *cum_ion = nullptr, *cum_att = nullptr;
-    int* pc_k = nullptr;
+    unsigned long long *n3 = nullptr, *cum_ion = nullptr, *cum_att = nullptr;
     long long* L = nullptr;
     unsigned long long* mom = nullptr;
     long long* cnt = nullptr;
-    unsigned long long *partial = nullptr, *partial_ps = nullptr;
     SwarmCtl* ctl = nullptr;
     double *values = nullptr, *errors = nullptr, *work = nullptr;
   } sw;
@@ -157,7 +155,7 @@ void free_pend(PendSoa& q);
 void free_swarm(pcmcc_ctx* c);
 int alloc_soa(pcmcc_ctx* c, Soa& b, uint64_t n);
 int alloc_pend(pcmcc_ctx* c, PendSoa& q, uint64_t n, bool with_sw);
-int ensure_swarm(pcmcc_ctx* c, int S, uint64_t slots, int J, int grid);
+int ensure_swarm(pcmcc_ctx* c, int S, uint64_t slots, int J);
 // A schedule resolved against the kernel's resources: every field set.
 struct StepLaunch {
   int block, bpc, refill, chunk, grid;

@@ -14,15 +14,12 @@
 // step (keep with probability 2^-k, or duplicate).  Moments are summed
 // exactly in 128-bit fixed point, so they do not depend on the order in
 // which particles land in the buffers.
-#include <hip/hip_cooperative_groups.h>
 #include <hip/hip_runtime.h>
 
 #include "pcmcc_device.hpp"
 #include "pcmcc_flight.hpp"
 #include "pcmcc_internal.hpp"
 #include "pcmcc_mover.hpp"
-
-namespace cg = cooperative_groups;
 
 namespace pcmcc {
 
@@ -200,28 +197,42 @@ constexpr int kMomExp[kNMom] = {0, 53, 53, 53, 53, 53, 25, 25, 25, 24, 24, 36, 0
 constexpr double kMomLim[kNMom] = {2.0, 1.0, 1.0, 1.0, 1.0, 1.0, 0x1p29, 0x1p29, 0x1p29, 0x1p30, 0x1p30,
                                     0x1p18, 0x1p53, 0x1p53};
 
-// Block-level exclusive scan of per-swarm tile counts into LDS prefix[0..S].
-__device__ void tile_prefix(const unsigned long long* n, int S, int tile, uint32_t* prefix, uint32_t* tmp) {
-  const int T = blockDim.x;
+// Block-level exclusive scan of per-swarm tile counts into LDS prefix[0..S]
+// (a wave scan of each thread's sum, then the waves' totals; tmp: one word per
+// wave).  n is plain memory written before the last grid barrier.
+__device__ void tile_prefix(const unsigned long long* __restrict__ n, int S, int tile, uint32_t* prefix,
+                            uint32_t* tmp) {
+  const int T = blockDim.x, lane = (int)lane_id(), wave = (int)(threadIdx.x >> 6);
   const int per = (S + T - 1) / T;
-  const int lo = threadIdx.x * per, hi = min(lo + per, S);
+  const int lo = min((int)threadIdx.x * per, S), hi = min(lo + per, S);
   uint32_t sum = 0;
-  for (int s = lo; s < hi; ++s) sum += (uint32_t)((ld_acq(&n[s]) + tile - 1) / tile);
-  tmp[threadIdx.x] = sum;
-  __syncthreads();
-  for (int off = 1; off < T; off <<= 1) {
-    const uint32_t v = threadIdx.x >= (unsigned)off ? tmp[threadIdx.x - off] : 0u;
-    __syncthreads();
-    tmp[threadIdx.x] += v;
-    __syncthreads();
+  for (int s = lo; s < hi; ++s) sum += (uint32_t)((n[s] + tile - 1) / tile);
+  uint32_t incl = sum;
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t o = __shfl_up(incl, d, 64);
+    if (lane >= d) incl += o;
   }
-  uint32_t run = threadIdx.x ? tmp[threadIdx.x - 1] : 0u;
+  if (lane == 63) tmp[wave] = incl;
+  __syncthreads();
+  uint32_t run = incl - sum;
+  for (int w = 0; w < wave; ++w) run += tmp[w];
   for (int s = lo; s < hi; ++s) {
     prefix[s] = run;
-    run += (uint32_t)((ld_acq(&n[s]) + tile - 1) / tile);
+    run += (uint32_t)((n[s] + tile - 1) / tile);
   }
-  if (threadIdx.x == T - 1) prefix[S] = tmp[T - 1];
+  if (threadIdx.x == (unsigned)T - 1) prefix[S] = run;
   __syncthreads();
+}
+
+// Population control of a swarm of n electrons that started with n0: 0, the
+// k > 0 of "keep with probability 2^-k", or -1 for "duplicate".
+__device__ __forceinline__ int control_k(unsigned long long n, long long n0) {
+  if ((long long)n > 2 * n0) {
+    int k = 1;
+    while (ldexp((double)n, -k) > 2.0 * (double)n0) ++k;
+    return k;
+  }
+  return n > 0 && 2 * (long long)n < n0 ? -1 : 0;
 }
 
 __device__ __forceinline__ int swarm_of(const uint32_t* prefix, int S, uint32_t g) {
@@ -255,16 +266,58 @@ __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
 }
 
 // ---------------------------------------------------------------------------
+// The step loop: phases, barriers and counters as in the PIC step's
+// (grid_barrier; a step without a sample and without newborns has one
+// barrier).  The swarms' electron counts rotate through three rows (n3), and
+// every block forms the population control from them by itself, so nothing
+// waits for one block to commit the swarms one by one.
+enum SwarmCode : uint32_t { SWARM_NEWBORN = 0, SWARM_SAMPLE = 1, SWARM_DONE = 2, SWARM_REJECTED = 3 };
+
+__device__ __forceinline__ void swarm_commit(const SwarmArgs& A, uint32_t* v) {
+  SwarmCtl* ctl = A.ctl;
+  const unsigned of = ld_relaxed(&ctl->overflow.v);
+  if (of) {
+    ctl->status = (of & OVF_LIMIT) ? PCMCC_ELIMIT : PCMCC_ECAPACITY;
+    v[0] = SWARM_REJECTED;
+  } else {
+    ctl->steps_done += 1;
+    v[0] = SWARM_DONE;
+  }
+  for (int q = 0; q < 2; ++q) {
+    st_relaxed(&ctl->pend[q].v, 0ull);
+    st_relaxed(&ctl->take[q].v, 0ull);
+  }
+}
+
+__device__ __forceinline__ void swarm_advance(const SwarmArgs& A, uint32_t* v, int p, bool sample) {
+  SwarmCtl* ctl = A.ctl;
+  const uint64_t np = ld_relaxed(&ctl->pend[p & 1].v);
+  if (np > 0 && p < kMaxGenerations) {
+    st_relaxed(&ctl->take[p & 1].v, 0ull);
+    st_relaxed(&ctl->pend[(p & 1) ^ 1].v, 0ull);
+    v[0] = SWARM_NEWBORN;
+    v[1] = (uint32_t)(np < A.pend_cap ? np : A.pend_cap);
+    return;
+  }
+  if (np > 0) atomicOr(&ctl->overflow.v, OVF_LIMIT);
+  if (sample) {
+    v[0] = SWARM_SAMPLE;
+    return;
+  }
+  swarm_commit(A, v);
+}
+
 template <int BS, int REFILL, int ROW>
 __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) void k_swarm_steps(SwarmArgs A) {
   extern __shared__ float smem[];
-  cg::grid_group grid = cg::this_grid();
+  __shared__ uint32_t s_pub[kBarWords];
+  __shared__ unsigned long long s_tot[NCNT + 1];  // counters of the committed steps, then the particle-steps
   const Tab T = stage_tables(A.T, A.S, smem);
   const int S = A.n_swarms;
   // LDS after the tables: per-wave staging lists, per-swarm acceleration [S]
   // (double), region base and capacity [S] (the refills and the finishers
   // read them from here, not from global memory), prefix [S+1], scan scratch
-  // [BS], |acceleration| [S] and population-control exponent [S].
+  // [BS / 64], |acceleration| [S] and population-control exponent [S].
   WaveStage* L = reinterpret_cast<WaveStage*>(smem + pic_stage_offset_floats(A.T)) + (threadIdx.x >> 6);
   double* az_d = reinterpret_cast<double*>(reinterpret_cast<WaveStage*>(smem + pic_stage_offset_floats(A.T)) +
                                            BS / 64);
@@ -272,7 +325,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) void k_
   uint64_t* cap_l = base_l + S;
   uint32_t* prefix = (uint32_t*)(cap_l + S);
   uint32_t* tmp = prefix + (S + 1);
-  float* az_l = (float*)(tmp + BS);
+  float* az_l = (float*)(tmp + BS / 64);
   int* pck = (int*)(az_l + S);
   __shared__ long long red[kNMom][BS / 64];
   __shared__ unsigned long long acc_lo[kNMom];
@@ -283,6 +336,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) void k_
     base_l[s] = A.base[s];
     cap_l[s] = A.cap_s[s];
   }
+  if (threadIdx.x <= NCNT) s_tot[threadIdx.x] = 0ull;
   __syncthreads();
   const SwarmField F{az_d, az_l, A.key};
   const auto* ka = (const __attribute__((address_space(4))) SwarmArgs*)__builtin_amdgcn_kernarg_segment_ptr();
@@ -291,51 +345,64 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) void k_
   const unsigned lane = lane_id();
   const uint32_t wpb = BS / 64;
   SwarmCtl* ctl = A.ctl;
+  uint32_t gen = 0;  // barriers so far
+  auto word = [&](int q) { return __builtin_amdgcn_readfirstlane(s_pub[q]); };
 
   for (int st = 0; st < A.n_steps; ++st) {
-    if (ld_acq(&ctl->stop)) break;
-    const int sel = __builtin_amdgcn_readfirstlane(ld_acq(&ctl->cur_sel));  // grid-uniform
-    const Soa nxt = A.buf[sel ^ 1];
+    const int sel = st & 1;
     const KArg<Soa> cur_k{&ka->buf[sel]}, nxt_k{&ka->buf[sel ^ 1]};
     const uint32_t step = (uint32_t)st;
-    for (int s = threadIdx.x; s < S; s += BS) pck[s] = ld_acq(&A.pc_k[s]);
-    tile_prefix(A.n_cur, S, 1, prefix, tmp);
+    const unsigned long long* n_cur = A.n3 + (size_t)(st % 3) * S;
+    unsigned long long* n_nxt = A.n3 + (size_t)((st + 1) % 3) * S;
+    for (int s = threadIdx.x; s < S; s += BS) {
+      const int k = A.pop_control ? control_k(n_cur[s], A.n0[s]) : 0;
+      pck[s] = k;
+      if (blockIdx.x == 0) {
+        A.L[s] += k;
+        A.n3[(size_t)((st + 2) % 3) * S + s] = 0;
+      }
+    }
+    tile_prefix(n_cur, S, 1, prefix, tmp);
     Cnt cnt;
 #pragma unroll
     for (int k = 0; k < NCNT; ++k) cnt.v[k] = 0;
     uint32_t psteps = 0;
-    const SwarmPlace fin{nxt_k, base_l, cap_l, A.n_nxt, A.cum_att, &ctl->overflow};
+    const SwarmPlace fin{nxt_k, base_l, cap_l, n_nxt, A.cum_att, &ctl->overflow.v};
+    const bool sample = ((st + 1) % A.sample_every) == 0 && (st + 1) / A.sample_every <= A.n_samples;
 
     // Phase 1: each swarm's electrons, after population control, from t = 0.
     {
-      const BirthSink sink{{&ka->pend[0]}, &ctl->pend[0], A.pend_cap, &ctl->overflow, 0u, no_events};
+      const BirthSink sink{{&ka->pend[0]}, &ctl->pend[0].v, A.pend_cap, &ctl->overflow.v, 0u, no_events};
       const SwarmLoad src{cur_k, base_l, prefix, pck, S, A.key, step, sink, &psteps};
-      fly_all<REFILL, ROW, false>((uint64_t)prefix[S], &ctl->take[0], chunk_k, (double)A.dt, F, T, A.S, step, cnt, sink,
+      fly_all<REFILL, ROW, false>((uint64_t)prefix[S], &ctl->take[0].v, chunk_k, (double)A.dt, F, T, A.S, step, cnt, sink,
                       A.cum_ion, L, src, fin);
     }
-    grid.sync();
+    grid_barrier(&ctl->bar, gen, s_pub, [&](uint32_t* v) { swarm_advance(A, v, 0, sample); });
 
     // Phase 2: newborns and duplicates of all swarms, generation by generation.
-    for (int g = 0;; ++g) {
-      const uint64_t np_raw = ld_acq(&ctl->pend[g]);
-      if (np_raw == 0) break;
-      if (g >= kMaxGenerations) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) atomicOr(&ctl->overflow, OVF_LIMIT);
-        break;
-      }
-      const uint64_t np = np_raw < A.pend_cap ? np_raw : A.pend_cap;
-      const BirthSink sink{{&ka->pend[(g + 1) & 1]}, &ctl->pend[g + 1], A.pend_cap, &ctl->overflow, 0u, no_events};
+    for (int g = 0; word(0) == SWARM_NEWBORN; ++g) {
+      const uint32_t np = word(1);
+      const BirthSink sink{{&ka->pend[(g + 1) & 1]}, &ctl->pend[(g + 1) & 1].v, A.pend_cap, &ctl->overflow.v, 0u,
+                           no_events};
       const SwarmPend src{{&ka->pend[g & 1]}};
-      fly_all<REFILL, ROW, false>(np, &ctl->take[g + 1], chunk_k, (double)A.dt, F, T, A.S, step, cnt, sink, A.cum_ion, L, src,
-                      fin);
-      grid.sync();
+      fly_all<REFILL, ROW, false>(np, &ctl->take[(g + 1) & 1].v, chunk_k, (double)A.dt, F, T, A.S, step, cnt, sink,
+                                  A.cum_ion, L, src, fin);
+      grid_barrier(&ctl->bar, gen, s_pub, [&](uint32_t* v) { swarm_advance(A, v, g + 1, sample); });
     }
 
     // Phase 3: moments of the new population (sample steps), exact sums.
-    const bool sample = ((st + 1) % A.sample_every) == 0 && (st + 1) / A.sample_every <= A.n_samples;
-    if (sample) {
+    if (word(0) == SWARM_SAMPLE) {
+      const Soa nxt = nxt_k.get();
       const int j = (st + 1) / A.sample_every - 1;
-      tile_prefix(A.n_nxt, S, BS, prefix, tmp);
+      if (blockIdx.x == 0)
+        for (int s = threadIdx.x; s < S; s += BS) {
+          long long* cc = A.cnt_out + ((size_t)s * A.n_samples + j) * 4;
+          cc[0] = (long long)n_nxt[s];
+          cc[1] = A.L[s];
+          cc[2] = (long long)A.cum_ion[s];
+          cc[3] = (long long)A.cum_att[s];
+        }
+      tile_prefix(n_nxt, S, BS, prefix, tmp);
       const uint32_t nt = prefix[S];
       const uint32_t t0 = (uint32_t)(((uint64_t)nt * blockIdx.x) / gridDim.x);
       const uint32_t t1 = (uint32_t)(((uint64_t)nt * (blockIdx.x + 1)) / gridDim.x);
@@ -357,7 +424,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) void k_
           cur_s = s;
           __syncthreads();
         }
-        const uint64_t n_s = ld_acq(&A.n_nxt[s]);
+        const uint64_t n_s = n_nxt[s];
         const uint64_t i = (uint64_t)(tt - prefix[s]) * BS + threadIdx.x;
         long long c[kNMom];
 #pragma unroll
@@ -387,7 +454,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) void k_
 #pragma unroll
           for (int m = 0; m < kNMom; ++m) {
             const double v = val[m];
-            if (!(fabs(v) < kMomLim[m])) atomicOr(&ctl->overflow, OVF_LIMIT);
+            if (!(fabs(v) < kMomLim[m])) atomicOr(&ctl->overflow.v, OVF_LIMIT);
             c[m] = __double2ll_rn(ldexp(v, kMomExp[m]));
           }
         }
@@ -413,77 +480,19 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) void k_
         unsigned long long* dst = A.mom + (((size_t)cur_s * A.n_samples + j) * kNMom + threadIdx.x) * 2;
         add128_atomic(dst, acc_lo[threadIdx.x], acc_hi[threadIdx.x]);
       }
+      grid_barrier(&ctl->bar, gen, s_pub, [&](uint32_t* v) { swarm_commit(A, v); });
     }
-    block_counters(cnt, A.partial);
-    if (threadIdx.x == 0) A.partial_ps[blockIdx.x] = 0;
-    __syncthreads();
-    {
-      const uint32_t w = wave_sum_u32(psteps);
-      if (lane == 0) atomicAdd(&A.partial_ps[blockIdx.x], (unsigned long long)w);
+    if (word(0) == SWARM_REJECTED) break;
+#pragma unroll
+    for (int k = 0; k < NCNT; ++k) {
+      const uint32_t t = wave_sum_dpp(cnt.v[k]);
+      if (lane == 0) atomicAdd(&s_tot[k], (unsigned long long)t);
     }
-    grid.sync();
-
-    // Commit (block 0): per-swarm counts, sample counters, population control.
-    if (blockIdx.x == 0) {
-      const unsigned of = ld_acq(&ctl->overflow);
-      for (int s = threadIdx.x; s < S; s += BS) {
-        const unsigned long long n_new = ld_acq(&A.n_nxt[s]);
-        if (sample) {
-          const int j = (st + 1) / A.sample_every - 1;
-          long long* cc = A.cnt_out + ((size_t)s * A.n_samples + j) * 4;
-          cc[0] = (long long)n_new;
-          cc[1] = A.L[s];
-          cc[2] = (long long)ld_acq(&A.cum_ion[s]);
-          cc[3] = (long long)ld_acq(&A.cum_att[s]);
-        }
-        int k = 0;
-        const long long n0 = A.n0[s];
-        if (A.pop_control) {
-          if ((long long)n_new > 2 * n0) {
-            k = 1;
-            while (ldexp((double)n_new, -k) > 2.0 * (double)n0) ++k;
-            A.L[s] += k;
-          } else if (n_new > 0 && 2 * (long long)n_new < n0) {
-            k = -1;
-            A.L[s] -= 1;
-          }
-        }
-        if (!of) {
-          A.pc_k[s] = k;
-          A.n_cur[s] = n_new;
-        }
-        A.n_nxt[s] = 0;
-      }
-      __shared__ unsigned long long sums[NCNT + 1];
-      if (threadIdx.x <= NCNT) sums[threadIdx.x] = 0;
-      __syncthreads();
-      for (int k = 0; k <= NCNT; ++k) {
-        unsigned long long acc = 0;
-        for (unsigned b = threadIdx.x; b < gridDim.x; b += BS)
-          acc += k < NCNT ? A.partial[(size_t)b * NCNT + k] : A.partial_ps[b];
-        for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-        if (lane == 0) atomicAdd(&sums[k], acc);
-      }
-      __syncthreads();
-      if (threadIdx.x == 0) {
-        if (of) {
-          ctl->stop = 1;
-          ctl->status = (of & OVF_LIMIT) ? PCMCC_ELIMIT : PCMCC_ECAPACITY;
-        } else {
-          ctl->cur_sel = sel ^ 1;
-          ctl->steps_done += 1;
-          ctl->particle_steps += sums[NCNT];
-          for (int k = 0; k < NCNT; ++k) ctl->tot[k] += sums[k];
-        }
-        ctl->overflow = 0;
-        for (int g = 0; g <= kMaxGenerations; ++g) {
-          ctl->pend[g] = 0;
-          ctl->take[g] = 0;
-        }
-      }
-    }
-    grid.sync();
+    const uint32_t t = wave_sum_dpp(psteps);
+    if (lane == 0) atomicAdd(&s_tot[NCNT], (unsigned long long)t);
   }
+  __syncthreads();
+  if (threadIdx.x <= NCNT && s_tot[threadIdx.x]) atomicAdd(&ctl->tot[threadIdx.x].v, s_tot[threadIdx.x]);
 }
 
 // Initial swarms: n0[s] electrons at rest at the origin, ids 0..n0-1.
@@ -613,7 +622,7 @@ __global__ void k_swarm_estimate(const unsigned long long* mom, const long long*
 // ---------------------------------------------------------------------------
 size_t swarm_lds_bytes(const TableView& T, int S, int block) {
   return pic_stage_offset_floats(T) * sizeof(float) + (size_t)(block / 64) * sizeof(WaveStage) + (size_t)S * 8 +
-         (size_t)S * 16 + (size_t)(S + 1) * 4 + (size_t)block * 4 + (size_t)S * 4 + (size_t)S * 4;
+         (size_t)S * 16 + (size_t)(S + 1) * 4 + (size_t)(block / 64) * 4 + (size_t)S * 4 + (size_t)S * 4;
 }
 
 template <int BS, int ROW>
