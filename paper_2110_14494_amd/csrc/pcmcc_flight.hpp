@@ -55,17 +55,25 @@ enum FlightEvent : int { EV_GO = 0, EV_DONE = 1, EV_ATTACHED = 2, EV_LIMIT = 3 }
 constexpr uint32_t kStage = 64;
 constexpr uint32_t kFlushAt = 48;  // (tuned: 32 -> 670 ms, 48 -> 657 ms per streamer call)
 
+// A newborn's generation within the step (1: child of an electron that began
+// the step) travels with its group in one word.  An electron's `src` below
+// kSrcBorn is its finisher's tag, from there on it is kSrcBorn + generation.
+constexpr uint32_t kSrcBorn = 64;
+constexpr uint32_t kTagBits = 16;  // groups: at most 4096 swarms
+__device__ __forceinline__ uint32_t tag_of(uint32_t packed) { return packed & ((1u << kTagBits) - 1u); }
+__device__ __forceinline__ uint32_t generation_of(uint32_t packed) { return packed >> kTagBits; }
+
 struct WaveStage {
   // newborns as their parent left them: x, y, z, w, birth time; segment
-  // number, group, parent id and the newborn's energy (the rest is drawn at
-  // flush)
+  // number, group and generation, parent id and the newborn's energy (the
+  // rest is drawn when they start or are queued)
   float b[5][kStage];
   uint32_t bj[kStage];
   uint32_t btag[kStage];
   uint64_t bpid[kStage];
   double beps[kStage];
-  // finished electrons: x .. w, group, id (phase 1 of the PIC step: s[0]
-  // holds hole slots)
+  // finished electrons: x .. w, group, id (phase 1 of the PIC step: newborns
+  // that finished, and stag holds hole slots)
   float s[7][kStage];
   uint32_t stag[kStage];
   uint64_t sid[kStage];
@@ -148,9 +156,11 @@ struct StagedBirths {
   uint32_t step;
   SpeciesView S;
   unsigned long long* cum_ion;
-  uint32_t n;  // staged entries (wave-uniform)
+  uint32_t n;      // staged entries (wave-uniform)
+  uint32_t quota;  // newborns the wave may still start itself
 
-  // Called by the lanes that create a newborn; returns true if it was staged.
+  // Called by the lanes that create a newborn (tag: packed group and
+  // generation); returns true if it was staged.
   __device__ __forceinline__ bool push(float x, float y, float z, float w, float tb, uint32_t tag, uint64_t pid,
                                        uint32_t j, double eps_new) const {
     const uint32_t s = n + rank_in(__ballot(1));
@@ -171,11 +181,11 @@ struct StagedBirths {
     c.y = y;
     c.z = z;
     c.w = w;
-    make_child(F.key(tag), step, S, pid, j, eps_new, c);
+    make_child(F.key(tag_of(tag)), step, S, pid, j, eps_new, c);
     BirthSink qt = q;
     qt.tag = tag;
     qt.push(c, tb);
-    if (cum_ion) atomicAdd(&cum_ion[tag], 1ull);
+    if (cum_ion) atomicAdd(&cum_ion[tag_of(tag)], 1ull);
     const EventSink ev = q.evk.get();
     if (ev.ix) {
       const uint64_t es = wave_reserve(ev.n);
@@ -205,7 +215,7 @@ struct StagedBirths {
       const uint64_t slot = b + l;
       if (slot < q.cap) {
         PState c;
-        make_child(F.key(tag), step, S, L->bpid[l], L->bj[l], L->beps[l], c);
+        make_child(F.key(tag_of(tag)), step, S, L->bpid[l], L->bj[l], L->beps[l], c);
         const PendSoa Q = q.qk.get();
         if (Q.sw) Q.sw[slot] = tag;
         Q.x[slot] = L->b[0][l];
@@ -221,26 +231,65 @@ struct StagedBirths {
         atomicOr(q.overflow, OVF_CAPACITY);
       }
     }
-    if (cum_ion) group_count(cum_ion, tag, mine);
+    count(tag, mine, l, n);
+    n = 0;
+  }
+
+  // Whole wave: ionizations per group, and the positive ions, of the k staged
+  // births taken out (lane entry e, where `mine`, distinct in [e0, e0 + k)).
+  __device__ __forceinline__ void count(uint32_t tag, bool mine, uint32_t e, uint32_t k) const {
+    if (cum_ion) group_count(cum_ion, tag_of(tag), mine);
     const EventSink ev = q.evk.get();
-    if (ev.ix) {  // the positive ions of the flushed births
+    if (ev.ix) {
       unsigned long long eb = 0;
-      if (lane_id() == 0) eb = atomicAdd(ev.n, (unsigned long long)n);
+      if (lane_id() == 0) eb = atomicAdd(ev.n, (unsigned long long)k);
       const uint64_t e0 = ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(eb >> 32)) << 32) |
                           __builtin_amdgcn_readfirstlane((uint32_t)eb);
+      const uint64_t es = e0 + rank_in(__ballot(mine));
       if (mine) {
-        const uint64_t es = e0 + l;
         if (es < ev.cap) {
-          ev.ix[es] = L->b[0][l];
-          ev.iy[es] = L->b[1][l];
-          ev.iz[es] = L->b[2][l];
-          ev.iw[es] = L->b[3][l];
+          ev.ix[es] = L->b[0][e];
+          ev.iy[es] = L->b[1][e];
+          ev.iz[es] = L->b[2][e];
+          ev.iw[es] = L->b[3][e];
         } else {
           atomicOr(ev.overflow, OVF_CAPACITY);
         }
       }
     }
-    n = 0;
+  }
+
+  // Whole wave: the last k staged newborns start in the lanes with `mine` set
+  // (k of them).
+  // Past the wave's quota (a runaway step, which would outgrow any buffer)
+  // they are dropped and the step overflows.
+  template <class F_>
+  __device__ __forceinline__ void start(F_& f, bool mine, uint32_t k) {
+    if (quota < k) {
+      if (lane_id() == 0) atomicOr(q.overflow, OVF_CAPACITY);
+      n = 0;
+      return;
+    }
+    quota -= k;
+    const uint32_t e = n - k + rank_in(__ballot(mine));
+    uint32_t tag = 0u;
+    if (mine) {
+      tag = L->btag[e];
+      PState c;
+      make_child(F.key(tag_of(tag)), step, S, L->bpid[e], L->bj[e], L->beps[e], c);
+      c.x = L->b[0][e];
+      c.y = L->b[1][e];
+      c.z = L->b[2][e];
+      c.w = L->b[3][e];
+      if (generation_of(tag) <= (uint32_t)kMaxGenerations) {
+        flight_start(f, c, (double)L->b[4][e], kSrcBorn + generation_of(tag), tag_of(tag));
+        f.pre = philox_pre(F.key(f.tag), f.id, step);
+      } else {
+        atomicOr(q.overflow, OVF_LIMIT);
+      }
+    }
+    count(tag, mine, e, k);
+    n -= k;
   }
 };
 
@@ -251,7 +300,7 @@ struct Flight {
   float a_abs, da, w, nu_hat;
   uint64_t id;
   uint32_t j;           // number of the next segment (random-number counter)
-  uint32_t src;         // slot the electron came from
+  uint32_t src;         // finisher's tag, or kSrcBorn + generation of a newborn
   uint32_t r1, r2, r3;  // uniforms of the pending collision
   uint32_t tag;         // group of the electron (swarm index; 0 in the PIC step)
   PhiloxPre pre;        // the products its draws of this step share
@@ -410,7 +459,8 @@ __device__ __forceinline__ int flight_complete(Flight& f, const double3 an, cons
   const double eps_ion = 0.5 * (eps - thr);
   const double eps_new = kind == ELASTIC ? eps_el : (kind == EXCITATION ? eps - thr : eps_ion);
   if (scatter && kind == IONIZATION)
-    staged = births.push((float)f.x, (float)f.y, (float)f.z, f.w, (float)f.t, f.tag, f.id, f.j - 1, eps_ion);
+    staged = births.push((float)f.x, (float)f.y, (float)f.z, f.w, (float)f.t,
+                         f.tag | ((f.src < kSrcBorn ? 1u : f.src - kSrcBorn + 1u) << kTagBits), f.id, f.j - 1, eps_ion);
   const double sn = sqrt_nr(eps_new * tc.inv_k_d);
   f.vx = scatter ? sn * nx : f.vx;
   f.vy = scatter ? sn * ny : f.vy;
@@ -444,13 +494,13 @@ __device__ __forceinline__ int flight_complete(Flight& f, const double3 an, cons
 // (zero before the first wave starts).  cum_ion (nullable) counts ionizations per group.  Every
 // staged entry is written out before the function returns.
 template <int REFILL, int ROW, bool GUIDED, class Field, class Source, class Finish>
-__device__ __forceinline__ void fly_all(uint64_t n, unsigned long long* take, KArg<uint32_t> chunk, double dt,
+__device__ __forceinline__ void fly_all(bool local, uint32_t quota, uint64_t n, unsigned long long* take, KArg<uint32_t> chunk, double dt,
                                         const Field& F, const Tab& T, const SpeciesView& S, uint32_t step, Cnt& cnt,
                                         const BirthSink& sink, unsigned long long* cum_ion, WaveStage* L,
                                         const Source& source, const Finish& finish) {
   Flight f;
   f.mode = FM_IDLE;
-  StagedBirths<Field> births{L, sink, F, step, S, cum_ion, 0u};
+  StagedBirths<Field> births{L, sink, F, step, S, cum_ion, 0u, quota};
   uint32_t n_done = 0;  // entries of the finish list
   uint64_t pool_next = 0, pool_end = 0;
   uint32_t chunk_tag = 0;  // finisher's tag of the current chunk
@@ -494,7 +544,15 @@ __device__ __forceinline__ void fly_all(uint64_t n, unsigned long long* take, KA
           n_done = 0;
         }
       }
-      // Start new electrons in the free lanes.
+      // Start new electrons in the free lanes: this wave's newborns, then
+      // the work of the phase.
+      if (pool_next == pool_end && seen >= n) dry = true;
+      if (local && (births.n >= (uint32_t)REFILL || (dry && births.n > 0))) {
+        const uint64_t idle = __ballot(f.mode == FM_IDLE);
+        const uint32_t n_idle = (uint32_t)__popcll(idle);
+        const uint32_t k = births.n < n_idle ? births.n : n_idle;
+        births.start(f, f.mode == FM_IDLE && rank_in(idle) < k, k);
+      }
       if (!dry) {
         const uint64_t idle = __ballot(f.mode == FM_IDLE);
         const uint32_t n_idle = (uint32_t)__popcll(idle);
@@ -548,7 +606,7 @@ __device__ __forceinline__ void fly_all(uint64_t n, unsigned long long* take, KA
     // Leave only when the work counter is exhausted: a refill may leave every
     // lane idle (a swarm's population control drops the electrons it loads),
     // and the next iteration then refills again.
-    if (dry && __ballot(f.mode != FM_IDLE) == 0) break;
+    if (dry && __ballot(f.mode != FM_IDLE) == 0 && !(local && births.n > 0)) break;
     bool born = false;
     if (f.mode == FM_FLY || f.mode == FM_NEW) {
       typename Field::Where where;
@@ -579,6 +637,7 @@ __device__ __forceinline__ void fly_all(uint64_t n, unsigned long long* take, KA
   }
   births.flush();
   if (n_done > 0) finish.flush(L, n_done);
+  finish.end(L);
 }
 
 }  // namespace pcmcc

@@ -80,6 +80,7 @@ struct Ctl {
   long long steps_done;
   int cur_sel;  // 0: the caller's arrays are current, 1: the scratch buffer
   int status;
+  unsigned long long ev_n[2];  // event counts after the last committed step
   CtlLine tot[NCNT];
 };
 

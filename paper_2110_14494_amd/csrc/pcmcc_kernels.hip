@@ -38,24 +38,23 @@ struct SoaSource {
   __device__ __forceinline__ void load(uint64_t i, Flight& f, uint32_t) const {
     PState p;
     load_p(sk.get(), i, p);
-    flight_start(f, p, 0.0, (uint32_t)i);
+    flight_start(f, p, 0.0, 0u);
   }
 };
 
 // Phase 2 source: a newborn queue, each electron from its birth time.
 struct PendSource {
   KArg<PendSoa> sk;
+  uint32_t born;  // kSrcBorn + generation
   __device__ __forceinline__ uint32_t hint(uint64_t) const { return 0u; }
   __device__ __forceinline__ void load(uint64_t i, Flight& f, uint32_t) const {
     PState p;
     float tb;
     load_pend(sk.get(), i, p, tb);
-    flight_start(f, p, (double)tb, (uint32_t)i);
+    flight_start(f, p, (double)tb, born);
   }
 };
 
-// Phase 1 destination: a survivor keeps its slot in the next buffer; a
-// removed electron leaves a hole there (hole slots are staged per wave).
 // A negative ion where an electron was attached (self-consistent step only).
 __device__ __forceinline__ void record_attachment(const EventSink& ev, const Flight& f) {
   const uint64_t es = wave_reserve(&ev.n[1]);
@@ -69,120 +68,9 @@ __device__ __forceinline__ void record_attachment(const EventSink& ev, const Fli
   }
 }
 
-// Phase 1 destination: the survivors of a chunk of slots the wave took are
-// written to the front of that chunk's range in the next buffer, in the
-// order they finish; once every electron of the chunk has finished, the rest
-// of its range is a run of holes (staged per wave).  The chunks a wave has
-// open are kept in its ring in LDS; an electron's tag is its chunk's ring
-// entry.  Writing each chunk's survivors consecutively keeps a few partly
-// written lines per chunk open in the cache instead of one per survivor.
-struct ChunkRing {
-  static constexpr uint32_t kR = 64;  // more than the 64 lanes can keep open, plus the chunk being loaded
-  uint64_t base[kR];
-  uint32_t size[kR], cursor[kR], remaining[kR];
-  uint32_t head;
-  uint32_t pad;
-  __device__ __forceinline__ void reset() {
-    remaining[lane_id()] = 0u;
-    if (lane_id() == 0) head = 0u;
-  }
-};
-
-struct KeepInPlace {
-  KArg<GridView> G;
-  KArg<Soa> nxt;
-  uint32_t* holes;
-  unsigned long long* n_holes;
-  KArg<EventSink> ev;
-  ChunkRing* R;  // the wave's ring (LDS)
-  __device__ __forceinline__ bool can_open() const {
-    const uint32_t h = __builtin_amdgcn_readfirstlane(R->head);
-    return __builtin_amdgcn_readfirstlane(R->remaining[h]) == 0u;
-  }
-  __device__ __forceinline__ uint32_t open_chunk(uint64_t first, uint32_t size) const {
-    const uint32_t h = __builtin_amdgcn_readfirstlane(R->head);
-    if (lane_id() == 0) {
-      R->base[h] = first;
-      R->size[h] = size;
-      R->cursor[h] = 0u;
-      R->remaining[h] = size;
-      R->head = (h + 1u) % ChunkRing::kR;
-    }
-    return h;
-  }
-  __device__ __forceinline__ void tag(Flight& f, uint32_t t) const { f.src = t; }
-  // Stages the hole slots [first, first + k) of the next buffer.
-  __device__ __forceinline__ uint32_t push_holes(WaveStage* L, uint32_t n_staged, uint32_t first, uint32_t k) const {
-    uint32_t off = 0;
-    while (off < k) {
-      if (n_staged == kStage) {
-        flush(L, n_staged);
-        n_staged = 0;
-      }
-      const uint32_t take = k - off < kStage - n_staged ? k - off : kStage - n_staged;
-      if (lane_id() < take) reinterpret_cast<uint32_t*>(L->s[0])[n_staged + lane_id()] = first + off + lane_id();
-      n_staged += take;
-      off += take;
-    }
-    return n_staged;
-  }
-  __device__ __forceinline__ uint32_t done_all(const Flight& f, bool parked, Cnt& cnt, WaveStage* L,
-                                               uint32_t n_staged) const {
-    PState p;
-    bool alive = false;
-    if (parked) {
-      if (f.seg == EV_ATTACHED) {
-        const EventSink e = ev.get();
-        if (e.ax) record_attachment(e, f);
-      }
-      p = flight_record(f);
-      alive = f.seg == EV_DONE;
-      if (alive && !inside(G.get(), p)) {
-        alive = false;
-        cnt.v[C_LOST]++;
-      }
-    }
-    // One round per chunk among the finishing electrons: the survivors take
-    // the chunk's next slots, and a chunk whose electrons have all finished
-    // hands the rest of its range to the hole list.
-    const uint32_t lane = lane_id();
-    uint64_t pending = __ballot(parked);
-    uint32_t slot = 0;
-    while (pending) {
-      const int leader = __ffsll((unsigned long long)pending) - 1;
-      const uint32_t r = __builtin_amdgcn_readlane(f.src, leader);
-      const uint64_t m_all = __ballot(parked && f.src == r);
-      const uint64_t m_alive = __ballot(parked && alive && f.src == r);
-      const uint32_t base = __builtin_amdgcn_readfirstlane((uint32_t)R->base[r]);
-      const uint32_t cur = __builtin_amdgcn_readfirstlane(R->cursor[r]);
-      const uint32_t rem = __builtin_amdgcn_readfirstlane(R->remaining[r]);
-      const uint32_t size = __builtin_amdgcn_readfirstlane(R->size[r]);
-      if ((m_alive >> lane) & 1) slot = base + cur + rank_in(m_alive);
-      const uint32_t cur2 = cur + (uint32_t)__popcll(m_alive);
-      const uint32_t rem2 = rem - (uint32_t)__popcll(m_all);
-      if (lane == 0) {
-        R->cursor[r] = cur2;
-        R->remaining[r] = rem2;
-      }
-      if (rem2 == 0u && cur2 < size) n_staged = push_holes(L, n_staged, base + cur2, size - cur2);
-      pending &= ~m_all;
-    }
-    if (alive) store_p(nxt.get(), slot, p);
-    return n_staged;
-  }
-  __device__ __forceinline__ void flush(WaveStage* L, uint32_t n) const {
-    unsigned long long base = 0;
-    if (lane_id() == 0) base = atomicAdd(n_holes, (unsigned long long)n);
-    const uint64_t b = ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(base >> 32)) << 32) |
-                       __builtin_amdgcn_readfirstlane((uint32_t)base);
-    const uint32_t l = lane_id();
-    if (l < n) holes[b + l] = reinterpret_cast<const uint32_t*>(L->s[0])[l];
-  }
-};
-
-// Phase 2 destination: a surviving newborn fills the next hole, or appends
-// after the current count once the holes are used up (placements are staged
-// per wave).
+// Destination of newborns: a survivor fills the next of the first n_holes
+// holes, or appends after the current count once these are used up
+// (placements are staged per wave).
 struct PlaceNewborn {
   KArg<GridView> G;
   KArg<Soa> nxt;
@@ -201,6 +89,7 @@ struct PlaceNewborn {
   __device__ __forceinline__ bool can_open() const { return true; }
   __device__ __forceinline__ uint32_t open_chunk(uint64_t, uint32_t) const { return 0u; }
   __device__ __forceinline__ void tag(Flight&, uint32_t) const {}
+  __device__ __forceinline__ void end(WaveStage*) const {}
   __device__ __forceinline__ uint32_t done_all(const Flight& f, bool parked, Cnt& cnt, WaveStage* L,
                                                uint32_t n_staged) const {
     bool staged = false;
@@ -255,6 +144,140 @@ struct PlaceNewborn {
   }
 };
 
+// Phase 1 destination: the survivors of a chunk of slots the wave took are
+// written to the front of that chunk's range in the next buffer, in the
+// order they finish; once every electron of the chunk has finished, the rest
+// of its range is a run of holes (staged per wave).  The chunks a wave has
+// open are kept in its ring in LDS; an electron's tag is its chunk's ring
+// entry.  Writing each chunk's survivors consecutively keeps a few partly
+// written lines per chunk open in the cache instead of one per survivor.
+struct ChunkRing {
+  static constexpr uint32_t kR = 64;  // more than the 64 lanes can keep open, plus the chunk being loaded
+  uint64_t base[kR];
+  uint32_t size[kR], cursor[kR], remaining[kR];
+  uint32_t head;
+  uint32_t n_born;  // staged newborns that finished
+  __device__ __forceinline__ void reset() {
+    remaining[lane_id()] = 0u;
+    if (lane_id() == 0) {
+      head = 0u;
+      n_born = 0u;
+    }
+  }
+};
+
+struct KeepInPlace {
+  KArg<GridView> G;
+  KArg<Soa> nxt;
+  uint32_t* holes;
+  unsigned long long* n_holes;
+  KArg<EventSink> ev;
+  ChunkRing* R;  // the wave's ring (LDS)
+  PlaceNewborn born;  // newborns the wave ran itself: staged in s and sid, R->n_born of them
+  __device__ __forceinline__ bool can_open() const {
+    const uint32_t h = __builtin_amdgcn_readfirstlane(R->head);
+    return __builtin_amdgcn_readfirstlane(R->remaining[h]) == 0u;
+  }
+  __device__ __forceinline__ uint32_t open_chunk(uint64_t first, uint32_t size) const {
+    const uint32_t h = __builtin_amdgcn_readfirstlane(R->head);
+    if (lane_id() == 0) {
+      R->base[h] = first;
+      R->size[h] = size;
+      R->cursor[h] = 0u;
+      R->remaining[h] = size;
+      R->head = (h + 1u) % ChunkRing::kR;
+    }
+    return h;
+  }
+  __device__ __forceinline__ void tag(Flight& f, uint32_t t) const { f.src = t; }
+  // Stages the hole slots [first, first + k) of the next buffer.
+  __device__ __forceinline__ uint32_t push_holes(WaveStage* L, uint32_t n_staged, uint32_t first, uint32_t k) const {
+    uint32_t off = 0;
+    while (off < k) {
+      if (n_staged == kStage) {
+        flush(L, n_staged);
+        n_staged = 0;
+      }
+      const uint32_t take = k - off < kStage - n_staged ? k - off : kStage - n_staged;
+      if (lane_id() < take) L->stag[n_staged + lane_id()] = first + off + lane_id();
+      n_staged += take;
+      off += take;
+    }
+    return n_staged;
+  }
+  __device__ __forceinline__ void end(WaveStage* L) const {
+    const uint32_t n = __builtin_amdgcn_readfirstlane(R->n_born);
+    if (n > 0) born.flush(L, n);
+  }
+  __device__ __forceinline__ uint32_t done_all(const Flight& f, bool parked, Cnt& cnt, WaveStage* L,
+                                               uint32_t n_staged) const {
+    const bool newborn = parked && f.src >= kSrcBorn;
+    if (__ballot(newborn) != 0) {
+      uint32_t n = __builtin_amdgcn_readfirstlane(R->n_born);
+      if (n + (uint32_t)__popcll(__ballot(newborn)) > kStage) {
+        born.flush(L, n);
+        n = 0;
+      }
+      n = born.done_all(f, newborn, cnt, L, n);
+      if (n >= kFlushAt) {
+        born.flush(L, n);
+        n = 0;
+      }
+      if (lane_id() == 0) R->n_born = n;
+      parked = parked && !newborn;
+    }
+    PState p;
+    bool alive = false;
+    if (parked) {
+      if (f.seg == EV_ATTACHED) {
+        const EventSink e = ev.get();
+        if (e.ax) record_attachment(e, f);
+      }
+      p = flight_record(f);
+      alive = f.seg == EV_DONE;
+      if (alive && !inside(G.get(), p)) {
+        alive = false;
+        cnt.v[C_LOST]++;
+      }
+    }
+    // One round per chunk among the finishing electrons: the survivors take
+    // the chunk's next slots, and a chunk whose electrons have all finished
+    // hands the rest of its range to the hole list.
+    const uint32_t lane = lane_id();
+    uint64_t pending = __ballot(parked);
+    uint32_t slot = 0;
+    while (pending) {
+      const int leader = __ffsll((unsigned long long)pending) - 1;
+      const uint32_t r = __builtin_amdgcn_readlane(f.src, leader);
+      const uint64_t m_all = __ballot(parked && f.src == r);
+      const uint64_t m_alive = __ballot(parked && alive && f.src == r);
+      const uint32_t base = __builtin_amdgcn_readfirstlane((uint32_t)R->base[r]);
+      const uint32_t cur = __builtin_amdgcn_readfirstlane(R->cursor[r]);
+      const uint32_t rem = __builtin_amdgcn_readfirstlane(R->remaining[r]);
+      const uint32_t size = __builtin_amdgcn_readfirstlane(R->size[r]);
+      if ((m_alive >> lane) & 1) slot = base + cur + rank_in(m_alive);
+      const uint32_t cur2 = cur + (uint32_t)__popcll(m_alive);
+      const uint32_t rem2 = rem - (uint32_t)__popcll(m_all);
+      if (lane == 0) {
+        R->cursor[r] = cur2;
+        R->remaining[r] = rem2;
+      }
+      if (rem2 == 0u && cur2 < size) n_staged = push_holes(L, n_staged, base + cur2, size - cur2);
+      pending &= ~m_all;
+    }
+    if (alive) store_p(nxt.get(), slot, p);
+    return n_staged;
+  }
+  __device__ __forceinline__ void flush(WaveStage* L, uint32_t n) const {
+    unsigned long long base = 0;
+    if (lane_id() == 0) base = atomicAdd(n_holes, (unsigned long long)n);
+    const uint64_t b = ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(base >> 32)) << 32) |
+                       __builtin_amdgcn_readfirstlane((uint32_t)base);
+    const uint32_t l = lane_id();
+    if (l < n) holes[b + l] = L->stag[l];
+  }
+};
+
 // ---------------------------------------------------------------------------
 // The step loop.  One cooperative launch runs all n_steps steps; grid-wide
 // barriers separate the phases of a step, and what decides the path (newborns
@@ -267,18 +290,38 @@ struct PlaceNewborn {
 // Four waves per SIMD (at most 128 registers a lane): the mover waits on
 // one gather per segment, and a fourth wave hides that latency better than
 // the registers the compiler would otherwise keep.
-enum StepCode : uint32_t { STEP_NEWBORN = 0, STEP_HOLES = 1, STEP_DONE = 2, STEP_LAST = 3, STEP_REJECTED = 4 };
+//
+// Newborns run in the wave that made them (fly_all's `local`) and append
+// after the current count; the holes of the step are then filled from the end
+// of the new population.  Until they are, the step needs up to `holes` slots
+// more than it ends with, so a step that overflows the capacity this way runs
+// again without it: newborns then go through the queue, generation by
+// generation, and fill the holes first, and that run decides.  The rest of
+// the call stays in this mode.
+enum StepCode : uint32_t {
+  STEP_NEWBORN = 0,   // queued newborns to run
+  STEP_FILL = 1,      // appended newborns to move into holes
+  STEP_HOLES = 2,     // holes to fill from the tail
+  STEP_DONE = 3,      // committed
+  STEP_LAST = 4,      // committed, back to the host
+  STEP_REJECTED = 5,  // the previous state stays
+  STEP_AGAIN = 6      // to be run again, newborns through the queue
+};
 
 // After phase p of the step (p generations done): the next thing to do.
 // v[0] the code, v[1] the newborns queued, v[2] the holes, v[3] the newborn
 // survivors, v[4] the population after a committed step.  One thread of the
 // grid runs it while every other waits.
-__device__ __forceinline__ void step_commit(const PicArgs& A, uint32_t* v, uint64_t n_cur) {
+__device__ __forceinline__ void step_commit(const PicArgs& A, uint32_t* v, uint64_t n_cur, bool local) {
   Ctl* ctl = A.ctl;
   const uint64_t h = ld_relaxed(&ctl->holes.v), nc = ld_relaxed(&ctl->child.v);
   const unsigned of = ld_relaxed(&ctl->overflow.v);
   v[0] = STEP_DONE;
-  if (of) {
+  if (of && local) {
+    v[0] = STEP_AGAIN;
+    if (A.ev.ix)  // the events of the step's first run
+      for (int q = 0; q < 2; ++q) st_relaxed(&A.ev.n[q], ctl->ev_n[q]);
+  } else if (of) {
     ctl->status = (of & OVF_LIMIT) ? PCMCC_ELIMIT : PCMCC_ECAPACITY;
     v[0] = STEP_REJECTED;
   } else {
@@ -288,6 +331,8 @@ __device__ __forceinline__ void step_commit(const PicArgs& A, uint32_t* v, uint6
     ctl->cur_sel ^= 1;
     ctl->steps_done += 1;
     v[4] = (uint32_t)n_new;
+    if (A.ev.ix)
+      for (int q = 0; q < 2; ++q) ctl->ev_n[q] = ld_relaxed(&A.ev.n[q]);
     if (A.n_limit && n_new > A.n_limit) {  // weights are due: back to the host
       ctl->status = kStatusWeightsDue;
       v[0] = STEP_LAST;
@@ -304,26 +349,27 @@ __device__ __forceinline__ void step_commit(const PicArgs& A, uint32_t* v, uint6
   }
 }
 
-__device__ __forceinline__ void step_advance(const PicArgs& A, uint32_t* v, int p, uint64_t n_cur) {
+__device__ __forceinline__ void step_advance(const PicArgs& A, uint32_t* v, int p, uint64_t n_cur, bool local) {
   Ctl* ctl = A.ctl;
-  const uint64_t np = ld_relaxed(&ctl->pend[p & 1].v);
-  if (np > 0 && p < kMaxGenerations) {
+  const uint64_t np = ld_relaxed(&ctl->pend[p & 1].v), h = ld_relaxed(&ctl->holes.v), nc = ld_relaxed(&ctl->child.v);
+  const unsigned of = ld_relaxed(&ctl->overflow.v);
+  if (np > 0 && p < kMaxGenerations && !(local && of)) {
     st_relaxed(&ctl->take[p & 1].v, 0ull);
     st_relaxed(&ctl->pend[(p & 1) ^ 1].v, 0ull);
     v[0] = STEP_NEWBORN;
     v[1] = (uint32_t)(np < A.pend_cap ? np : A.pend_cap);
-    v[2] = (uint32_t)ld_relaxed(&ctl->holes.v);
+    v[2] = (uint32_t)h;
     return;
   }
   if (np > 0) atomicOr(&ctl->overflow.v, OVF_LIMIT);
-  const uint64_t h = ld_relaxed(&ctl->holes.v), nc = ld_relaxed(&ctl->child.v);
-  if (nc < h && ld_relaxed(&ctl->overflow.v) == 0u) {
+  v[2] = (uint32_t)h;
+  v[3] = (uint32_t)nc;
+  if (np == 0 && !of && h > 0 && (local ? nc > 0 : nc < h))
+    v[0] = local ? STEP_FILL : STEP_HOLES;
+  else if (np == 0 && !of && nc < h)
     v[0] = STEP_HOLES;
-    v[2] = (uint32_t)h;
-    v[3] = (uint32_t)nc;
-    return;
-  }
-  step_commit(A, v, n_cur);
+  else
+    step_commit(A, v, n_cur, local);
 }
 
 template <int REFILL, int ROW>
@@ -348,8 +394,14 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
   auto word = [&](int q) { return __builtin_amdgcn_readfirstlane(s_pub[q]); };
   int sel = __builtin_amdgcn_readfirstlane(ctl->cur_sel);
   uint32_t n_cur = __builtin_amdgcn_readfirstlane((uint32_t)ctl->n_cur);  // capacity below 2^32
+  bool local = true;
+  // Newborns a wave may run itself in a phase: an even share of 64 full
+  // queues, the most that the queue would let through, and some.
+  const uint32_t quota = (uint32_t)min((unsigned long long)(A.pend_cap * kMaxGenerations) /
+                                               (gridDim.x * (blockDim.x >> 6)) + 4096ull,
+                                       0xFFFFFFFFull);
 
-  for (int s = 0; s < A.n_steps; ++s) {
+  for (int s = 0; s < A.n_steps;) {
     const KArg<Soa> cur_k{&ka->buf[sel]}, nxt_k{&ka->buf[sel ^ 1]};
     const KArg<GridView> grid_k{&ka->G};
     const KArg<EventSink> ev_k{&ka->ev};
@@ -363,26 +415,43 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
     {
       const BirthSink sink{{&ka->pend[0]}, &ctl->pend[0].v, A.pend_cap, &ctl->overflow.v, 0u, ev_k};
       const SoaSource src{cur_k};
-      const KeepInPlace fin{grid_k, nxt_k, A.holes, &ctl->holes.v, ev_k, ring};
+      const KeepInPlace fin{grid_k, nxt_k, A.holes, &ctl->holes.v, ev_k, ring,
+                            PlaceNewborn{grid_k, nxt_k, A.holes, 0, n_cur, A.cap, &ctl->child.v, &ctl->overflow.v, ev_k}};
       ring->reset();
-      fly_all<REFILL, ROW, true>(n_cur, &ctl->take[0].v, chunk_k, A.dt, F, T, A.S, step, cnt, sink, nullptr, L, src,
+      fly_all<REFILL, ROW, true>(local, quota, n_cur, &ctl->take[0].v, chunk_k, A.dt, F, T, A.S, step, cnt, sink, nullptr, L, src,
                                  fin);
     }
-    grid_barrier(&ctl->bar, gen, s_pub, [&](uint32_t* v) { step_advance(A, v, 0, n_cur); });
+    grid_barrier(&ctl->bar, gen, s_pub, [&](uint32_t* v) { step_advance(A, v, 0, n_cur, local); });
 
     // Phase 2: newborns, one generation at a time.  Survivors fill the holes
     // first, then append after the current count.
     for (int g = 0; word(0) == STEP_NEWBORN; ++g) {
-      const uint32_t np = word(1), h = word(2);
+      const uint32_t np = word(1), h = local ? 0u : word(2);
       const BirthSink sink{{&ka->pend[(g + 1) & 1]}, &ctl->pend[(g + 1) & 1].v, A.pend_cap, &ctl->overflow.v, 0u, ev_k};
-      const PendSource src{{&ka->pend[g & 1]}};
+      const PendSource src{{&ka->pend[g & 1]}, kSrcBorn + 1u + (uint32_t)g};
       const PlaceNewborn fin{grid_k, nxt_k, A.holes, h, n_cur, A.cap, &ctl->child.v, &ctl->overflow.v, ev_k};
-      fly_all<REFILL, ROW, true>(np, &ctl->take[(g + 1) & 1].v, chunk_k, A.dt, F, T, A.S, step, cnt, sink, nullptr, L,
+      fly_all<REFILL, ROW, true>(local, quota, np, &ctl->take[(g + 1) & 1].v, chunk_k, A.dt, F, T, A.S, step, cnt, sink, nullptr, L,
                                  src, fin);
-      grid_barrier(&ctl->bar, gen, s_pub, [&](uint32_t* v) { step_advance(A, v, g + 1, n_cur); });
+      grid_barrier(&ctl->bar, gen, s_pub, [&](uint32_t* v) { step_advance(A, v, g + 1, n_cur, local); });
     }
 
-    // Phase 3: holes not filled by newborns are filled from the tail.
+    // Phase 3: holes are filled by the last appended newborns, those not
+    // filled by newborns from the tail.
+    if (word(0) == STEP_FILL) {
+      const Soa nxt = nxt_k.get();
+      const uint64_t h = word(2), nc = word(3), m = h < nc ? h : nc;
+      for (uint64_t k = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; k < m; k += (uint64_t)gridDim.x * blockDim.x) {
+        PState p;
+        load_p(nxt, n_cur + nc - 1 - k, p);
+        store_p(nxt, A.holes[k], p);
+      }
+      grid_barrier(&ctl->bar, gen, s_pub, [&](uint32_t* v) {
+        v[0] = STEP_HOLES;
+        v[2] = (uint32_t)h;
+        v[3] = (uint32_t)nc;
+        if (nc >= h) step_commit(A, v, n_cur, local);
+      });
+    }
     if (word(0) == STEP_HOLES) {
       const Soa nxt = nxt_k.get();
       const uint64_t h = word(2), nc = word(3);
@@ -415,10 +484,14 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
           }
         }
       }
-      grid_barrier(&ctl->bar, gen, s_pub, [&](uint32_t* v) { step_commit(A, v, n_cur); });
+      grid_barrier(&ctl->bar, gen, s_pub, [&](uint32_t* v) { step_commit(A, v, n_cur, local); });
     }
     const uint32_t code = word(0);
-    if (code == STEP_REJECTED) break;  // the previous state stays
+    if (code == STEP_REJECTED) break;
+    if (code == STEP_AGAIN) {
+      local = false;
+      continue;
+    }
 #pragma unroll
     for (int k = 0; k < NCNT; ++k) {
       const uint32_t t = wave_sum_dpp(cnt.v[k]);
@@ -427,6 +500,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
     if (code == STEP_LAST) break;
     n_cur = word(4);
     sel ^= 1;
+    ++s;
   }
   __syncthreads();
   if (threadIdx.x < NCNT && s_tot[threadIdx.x]) atomicAdd(&ctl->tot[threadIdx.x].v, s_tot[threadIdx.x]);

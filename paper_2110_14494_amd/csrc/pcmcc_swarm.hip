@@ -88,7 +88,7 @@ struct SwarmLoad {
         PState d = p;
         d.id = (uint64_t)r.y | ((uint64_t)r.z << 32);
         BirthSink q = dup;
-        q.tag = (uint32_t)s;
+        q.tag = (uint32_t)s | (1u << kTagBits);
         q.push(d, 0.0f);
         (*psteps)++;
       }
@@ -108,7 +108,8 @@ struct SwarmPend {
     float tb;
     const PendSoa q = qk.get();
     load_pend(q, i, p, tb);
-    flight_start(f, p, (double)tb, 0u, q.sw[i]);
+    const uint32_t packed = q.sw[i];
+    flight_start(f, p, (double)tb, kSrcBorn + generation_of(packed), tag_of(packed));
   }
 };
 
@@ -122,6 +123,7 @@ struct SwarmPlace {
   unsigned long long* n_nxt;
   unsigned long long* cum_att;
   unsigned* overflow;
+  __device__ __forceinline__ void end(WaveStage*) const {}
   __device__ __forceinline__ bool can_open() const { return true; }
   __device__ __forceinline__ uint32_t open_chunk(uint64_t, uint32_t) const { return 0u; }
   __device__ __forceinline__ void tag(Flight&, uint32_t) const {}
@@ -345,6 +347,9 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) void k_
   const unsigned lane = lane_id();
   const uint32_t wpb = BS / 64;
   SwarmCtl* ctl = A.ctl;
+  // Newborns a wave may run itself in a phase: 64 full queues, the most that
+  // the queue would let through.
+  const uint32_t quota = (uint32_t)min((unsigned long long)(A.pend_cap * kMaxGenerations), 0xFFFFFFFFull);
   uint32_t gen = 0;  // barriers so far
   auto word = [&](int q) { return __builtin_amdgcn_readfirstlane(s_pub[q]); };
 
@@ -374,7 +379,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) void k_
     {
       const BirthSink sink{{&ka->pend[0]}, &ctl->pend[0].v, A.pend_cap, &ctl->overflow.v, 0u, no_events};
       const SwarmLoad src{cur_k, base_l, prefix, pck, S, A.key, step, sink, &psteps};
-      fly_all<REFILL, ROW, false>((uint64_t)prefix[S], &ctl->take[0].v, chunk_k, (double)A.dt, F, T, A.S, step, cnt, sink,
+      fly_all<REFILL, ROW, false>(true, quota, (uint64_t)prefix[S], &ctl->take[0].v, chunk_k, (double)A.dt, F, T, A.S, step, cnt, sink,
                       A.cum_ion, L, src, fin);
     }
     grid_barrier(&ctl->bar, gen, s_pub, [&](uint32_t* v) { swarm_advance(A, v, 0, sample); });
@@ -385,7 +390,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) void k_
       const BirthSink sink{{&ka->pend[(g + 1) & 1]}, &ctl->pend[(g + 1) & 1].v, A.pend_cap, &ctl->overflow.v, 0u,
                            no_events};
       const SwarmPend src{{&ka->pend[g & 1]}};
-      fly_all<REFILL, ROW, false>(np, &ctl->take[(g + 1) & 1].v, chunk_k, (double)A.dt, F, T, A.S, step, cnt, sink,
+      fly_all<REFILL, ROW, false>(true, quota, np, &ctl->take[(g + 1) & 1].v, chunk_k, (double)A.dt, F, T, A.S, step, cnt, sink,
                                   A.cum_ion, L, src, fin);
       grid_barrier(&ctl->bar, gen, s_pub, [&](uint32_t* v) { swarm_advance(A, v, g + 1, sample); });
     }
