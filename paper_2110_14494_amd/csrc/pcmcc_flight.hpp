@@ -472,8 +472,7 @@ __device__ __forceinline__ int flight_complete(Flight& f, const double3 an, cons
 // (tables of ROW floats per node, table_row(nproc)),
 // REFILL lanes at a time (see above), `chunk` (a power of two in [kChunkMin,
 // kChunkMax], read from the kernel arguments) electrons per work-counter
-// grab, or with GUIDED a shrinking share of the rest down to kChunkMin.  A
-// wave's first chunk is its own by position (no atomic): with the work
+// grab at most, and less as the work runs out.  A wave's first chunk is its own by position (no atomic): with the work
 // counter's same-address atomics, 13 ns each, 4096 waves would need 55 us
 // just to find out what there is to do, which is all that a newborn
 // generation of a few thousand electrons takes.
@@ -493,7 +492,7 @@ __device__ __forceinline__ int flight_complete(Flight& f, const double3 an, cons
 // arguments; `take` is the grid-wide work counter beyond the first chunks
 // (zero before the first wave starts).  cum_ion (nullable) counts ionizations per group.  Every
 // staged entry is written out before the function returns.
-template <int REFILL, int ROW, bool GUIDED, class Field, class Source, class Finish>
+template <int REFILL, int ROW, class Field, class Source, class Finish>
 __device__ __forceinline__ void fly_all(bool local, uint32_t quota, uint64_t n, unsigned long long* take, KArg<uint32_t> chunk, double dt,
                                         const Field& F, const Tab& T, const SpeciesView& S, uint32_t step, Cnt& cnt,
                                         const BirthSink& sink, unsigned long long* cum_ion, WaveStage* L,
@@ -507,13 +506,13 @@ __device__ __forceinline__ void fly_all(bool local, uint32_t quota, uint64_t n, 
   uint32_t src_hint = 0;   // source's hint for the current chunk
   const uint32_t lane = lane_id();
   // First chunks: one per wave, wave w of block b at place w gridDim + b, so
-  // that a short phase spreads over the blocks; half of an even share of the
-  // work, between kChunkMin and the schedule's chunk (a phase that fits one
+  // that a short phase spreads over the blocks; three quarters of an even share
+  // of the work (half of one: 27.4 instead of 26.8 ms on the streamer stage), between kChunkMin and the schedule's chunk (a phase that fits one
   // kChunkMin per wave needs no work counter at all).
   const uint32_t waves = gridDim.x * (blockDim.x >> 6);
   uint64_t first;  // electrons in all first chunks together
   {
-    const uint64_t share = n / (2u * (uint64_t)waves);
+    const uint64_t share = 3u * n / (4u * (uint64_t)waves);
     const uint32_t most = chunk.get();
     const uint32_t ch = share < (uint64_t)kChunkMin ? kChunkMin : (share < (uint64_t)most ? (uint32_t)share : most);
     const uint32_t w = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) * gridDim.x + blockIdx.x);
@@ -565,17 +564,18 @@ __device__ __forceinline__ void fly_all(bool local, uint32_t quota, uint64_t n, 
               break;
             }
             if (!finish.can_open()) break;  // the lanes stay idle until a chunk of this wave completes
-            // GUIDED: a share of what was left at this wave's previous grab,
-            // (n - seen) / (2 waves), between kChunkMin and the schedule's
-            // chunk, so that a phase ends on small chunks instead of leaving
-            // one wave a whole large chunk behind the others (the PIC step:
-            // 1 % on its large phases; the swarms' short steps lose more to
-            // the extra grabs than they gain).
-            uint32_t ch = chunk.get();
-            if (GUIDED) {
-              const uint64_t share = (n - seen) / (2u * (uint64_t)waves);
-              ch = share < (uint64_t)kChunkMin ? (uint32_t)kChunkMin : (share < ch ? (uint32_t)share : ch);
-            }
+            // An even share of what was left at this wave's previous grab,
+            // between kChunkMin and the schedule's chunk, so that a phase ends
+            // on small chunks instead of leaving one wave a whole large chunk
+            // behind the others: with fixed chunks of 512 a phase of 3.8e5
+            // swarm electrons took 235 us instead of about 110 (a batch of 64
+            // swarms 96 instead of 63 ms).  Half an even share costs a batch of
+            // 256 swarms 7 % in work-counter atomics (354 against 331 ms for
+            // 300 steps, as with fixed chunks).
+            const uint32_t most = chunk.get();
+            const uint64_t share = (n - seen) / (uint64_t)waves;
+            const uint32_t ch =
+                share < (uint64_t)kChunkMin ? kChunkMin : (share < (uint64_t)most ? (uint32_t)share : most);
             unsigned long long base = 0;
             if (lane == 0) base = atomicAdd(take, (unsigned long long)ch);
             const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)base);

@@ -418,7 +418,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
       const KeepInPlace fin{grid_k, nxt_k, A.holes, &ctl->holes.v, ev_k, ring,
                             PlaceNewborn{grid_k, nxt_k, A.holes, 0, n_cur, A.cap, &ctl->child.v, &ctl->overflow.v, ev_k}};
       ring->reset();
-      fly_all<REFILL, ROW, true>(local, quota, n_cur, &ctl->take[0].v, chunk_k, A.dt, F, T, A.S, step, cnt, sink, nullptr, L, src,
+      fly_all<REFILL, ROW>(local, quota, n_cur, &ctl->take[0].v, chunk_k, A.dt, F, T, A.S, step, cnt, sink, nullptr, L, src,
                                  fin);
     }
     grid_barrier(&ctl->bar, gen, s_pub, [&](uint32_t* v) { step_advance(A, v, 0, n_cur, local); });
@@ -430,7 +430,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
       const BirthSink sink{{&ka->pend[(g + 1) & 1]}, &ctl->pend[(g + 1) & 1].v, A.pend_cap, &ctl->overflow.v, 0u, ev_k};
       const PendSource src{{&ka->pend[g & 1]}, kSrcBorn + 1u + (uint32_t)g};
       const PlaceNewborn fin{grid_k, nxt_k, A.holes, h, n_cur, A.cap, &ctl->child.v, &ctl->overflow.v, ev_k};
-      fly_all<REFILL, ROW, true>(local, quota, np, &ctl->take[(g + 1) & 1].v, chunk_k, A.dt, F, T, A.S, step, cnt, sink, nullptr, L,
+      fly_all<REFILL, ROW>(local, quota, np, &ctl->take[(g + 1) & 1].v, chunk_k, A.dt, F, T, A.S, step, cnt, sink, nullptr, L,
                                  src, fin);
       grid_barrier(&ctl->bar, gen, s_pub, [&](uint32_t* v) { step_advance(A, v, g + 1, n_cur, local); });
     }
