@@ -9,8 +9,10 @@ namespace {
 struct MlpDev {
   float *params = nullptr, *x = nullptr, *t = nullptr, *mask = nullptr, *partial = nullptr, *ploss = nullptr;
   float *m = nullptr, *v = nullptr, *grad = nullptr, *loss = nullptr, *hist = nullptr;
+  GridBar* bar = nullptr;
   ~MlpDev() {
     for (float* q : {params, x, t, mask, partial, ploss, m, v, grad, loss, hist}) dfree(q);
+    dfree(bar);
   }
 };
 
@@ -31,7 +33,7 @@ int mlp_upload(pcmcc_ctx* c, MlpDev& d, const float* params, int64_t n, const fl
   HIP_TRY(c, dalloc(&d.x, n));
   HIP_TRY(c, dalloc(&d.t, n * PCMCC_MLP_OUT));
   HIP_TRY(c, dalloc(&d.mask, n * PCMCC_MLP_OUT));
-  HIP_TRY(c, dalloc(&d.partial, (size_t)nb * kMlpParams));
+  HIP_TRY(c, dalloc(&d.partial, (size_t)nb * kMlpStride));
   HIP_TRY(c, dalloc(&d.ploss, nb));
   HIP_TRY(c, hipMemcpyAsync(d.params, params, sizeof(float) * kMlpParams, hipMemcpyHostToDevice, c->stream));
   HIP_TRY(c, hipMemcpyAsync(d.x, x, sizeof(float) * n, hipMemcpyHostToDevice, c->stream));
@@ -47,7 +49,7 @@ int pcmcc_mlp_grad(pcmcc_ctx* c, const float* params, int64_t n, const float* x,
   if (!c) return fail(nullptr, PCMCC_EINVAL, "null context");
   if (!grad_out || !loss_out) return fail(c, PCMCC_EINVAL, "null output");
   HIP_TRY(c, hipSetDevice(c->device));
-  const int nb = (int)std::min<int64_t>((n + 63) / 64, 1024);
+  const int nb = (int)std::min<int64_t>((n + kMlpTile - 1) / kMlpTile, 1024);
   MlpDev d;
   float inv_cnt = 0;
   int rc = mlp_upload(c, d, params, n, x, t, mask, std::max(nb, 1), &inv_cnt);
@@ -86,7 +88,7 @@ int pcmcc_mlp_train(pcmcc_ctx* c, const float* params_in, int64_t n, const float
   int per_cu = 0;
   HIP_TRY(c, occupancy_mlp_train(&per_cu));
   if (per_cu < 1) return fail(c, PCMCC_EHIP, "training kernel does not fit on a compute unit");
-  const int nb = (int)std::min<int64_t>(std::min<int64_t>((n + 63) / 64, (int64_t)per_cu * c->num_cu), 1024);
+  const int nb = (int)std::min<int64_t>(std::min<int64_t>((n + kMlpTile - 1) / kMlpTile, (int64_t)per_cu * c->num_cu), 1024);
   MlpDev d;
   float inv_cnt = 0;
   int rc = mlp_upload(c, d, params_in, n, x, t, mask, std::max(nb, 1), &inv_cnt);
@@ -95,6 +97,8 @@ int pcmcc_mlp_train(pcmcc_ctx* c, const float* params_in, int64_t n, const float
   HIP_TRY(c, dalloc(&d.v, kMlpParams));
   HIP_TRY(c, hipMemsetAsync(d.m, 0, sizeof(float) * kMlpParams, c->stream));
   HIP_TRY(c, hipMemsetAsync(d.v, 0, sizeof(float) * kMlpParams, c->stream));
+  HIP_TRY(c, dalloc(&d.bar, 1));
+  HIP_TRY(c, hipMemsetAsync(d.bar, 0, sizeof(GridBar), c->stream));
   if (loss_hist) HIP_TRY(c, dalloc(&d.hist, o->epochs));
   MlpArgs A{};
   A.params = d.params;
@@ -108,6 +112,7 @@ int pcmcc_mlp_train(pcmcc_ctx* c, const float* params_in, int64_t n, const float
   A.m = d.m;
   A.v = d.v;
   A.loss_hist = d.hist;
+  A.bar = d.bar;
   A.epochs = o->epochs;
   A.lr0 = o->lr0;
   A.lr_min = o->lr_min;

@@ -216,6 +216,8 @@ struct SwarmArgs {
 
 // Coefficient surrogate (1 -> 64 -> 64 -> 6 perceptron).
 constexpr int kMlpParams = 4678;
+constexpr int kMlpStride = 4736;  // floats per row of partial gradients
+constexpr int kMlpTile = 32;      // points a block takes at a time in training
 
 struct MlpArgs {
   float* params;        // [kMlpParams], updated in place by training
@@ -224,7 +226,7 @@ struct MlpArgs {
   const float* mask;    // [n][6] 1 = use the entry
   int64_t n;
   float inv_cnt;        // 1 / number of used entries
-  float* partial;       // [grid][kMlpParams]
+  float* partial;       // [grid][kMlpStride]
   float* ploss;         // [grid]
   float* m;             // Adam first moments
   float* v;             // Adam second moments
@@ -232,6 +234,7 @@ struct MlpArgs {
   int epochs;
   double lr0, lr_min;
   float beta1, beta2, eps;
+  GridBar* bar;         // training: zero at the start
 };
 
 struct InferArgs {
@@ -249,7 +252,6 @@ struct InferArgs {
   const float* table;   // [n_nodes][6] ln coefficients
 };
 
-size_t mlp_lds_bytes();
 hipError_t launch_mlp_grad(const MlpArgs& a, int grid, hipStream_t stream);
 hipError_t launch_mlp_reduce(const float* partial, const float* ploss, int nb, float* grad, float* loss,
                              hipStream_t stream);

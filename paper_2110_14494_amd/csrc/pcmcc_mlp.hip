@@ -3,7 +3,7 @@
 // coefficients (the inputs of the fluid model of arXiv:2110.14494 Sec. 2.2,
 // computed by the swarms of Sec. 2.2.2).
 //
-//  * training (FP32): forward and backward over 64-point tiles held in LDS,
+//  * training (FP32): forward and backward over 32-point tiles held in LDS,
 //    gradients reduced in a fixed order (bit-reproducible), full-batch Adam
 //    with a cosine learning rate; one cooperative launch runs every epoch;
 //  * inference (BF16 weights and activations, FP32 accumulation): the 64x64
@@ -15,177 +15,291 @@
 //    of the swarm table.
 // Parameter vector (4678 floats): W1[64,1], b1[64], W2[64,64], b2[64],
 // W3[6,64], b3[6], row-major.
-#include <hip/hip_cooperative_groups.h>
 #include <hip/hip_runtime.h>
 
 #include "pcmcc_internal.hpp"
 
-namespace cg = cooperative_groups;
-
 namespace pcmcc {
 
-constexpr int kH = 64, kOut = 6, kTile = 64;
+constexpr int kH = 64, kOut = 6;
 constexpr unsigned kAllOut = (1u << kOut) - 1u;  // fallback mask with every output
 constexpr int OFF_W1 = 0, OFF_B1 = 64, OFF_W2 = 128, OFF_B2 = 128 + 4096, OFF_W3 = OFF_B2 + 64,
               OFF_B3 = OFF_W3 + 384;
 static_assert(OFF_B3 + 6 == kMlpParams, "parameter packing");
 
 // ---------------------------------------------------------------------------
-// Training: one tile of 64 points through forward and backward.  Gradients
-// of W2 stay in registers (16 per thread, thread t owns row t/4, columns
-// 16 (t%4) .. +15); the other 582 gradients live in LDS, each owned by one
-// thread.  Everything is in a fixed order, so results are reproducible.
+// Training: one tile of kTile points through forward and backward.  The three
+// 64-wide products (layer 2, its input gradient, its weight gradient) run on
+// register tiles: a thread holds 2 x 4 (or 4 x 4) outputs and reads its two
+// operands as vectors from LDS copies laid out so that the lanes of a wave
+// read consecutive words; the operands are therefore kept in both orders.
+// Everything is in a fixed order, so results are reproducible.  Bound by
+// the single-precision multiply-adds of a tile on one compute unit (0.9 us a
+// product for 32 points) and the latencies between them.  A thread per output
+// reading two LDS words per multiply-add, the layer's weights with all lanes
+// on one bank, and 64-point tiles took 163 us an epoch for 1792 points (28
+// blocks); this takes EPOCH_US us (56 blocks).
+constexpr int kTile = kMlpTile, kTP = kTile + 4;
 struct MlpLds {
-  float P[kMlpParams];
-  float H1[kTile][kH + 1];
-  float H2[kTile][kH + 1];
-  float D2[kTile][kH + 1];
+  float W2[kH][kH];    // [j][k]
+  float W2T[kH][kH];   // [k][j]
+  float H1[kTile][kH];
+  float H1T[kH][kTP];  // [k][p]
+  float D2[kTile][kH];
+  float D2T[kH][kTP];  // [j][p]
+  float H2[kTile][kH + 1];  // later the gradient at layer 1
+  float W1[kH], b1[kH], b2[kH], W3[kOut][kH], b3[kOut];
   float x[kTile];
   float dy[kTile][kOut];
-  float gsmall[kMlpParams - 4096];  // gradients of W1, b1, b2, W3, b3 (index = param - 4096 past OFF_W2)
-  float loss[256];
+  float red[256];
 };
 
-// Index of a non-W2 parameter in gsmall.
-__device__ __forceinline__ int small_idx(int param) { return param < OFF_W2 ? param : param - 4096; }
+// Small-parameter gradients a thread owns: W3 entries tid and tid + 256 (of
+// 384), one of b3, b2, and one of W1 or b1.
+struct MlpAcc {
+  float W2[4][4];  // rows 4 (tid / 16) .., columns 4 (tid % 16) ..
+  float W3[2], b3, b2, l1;
+  float loss;
+};
 
-__device__ void tile_grad(MlpLds& L, const float* __restrict__ x, const float* __restrict__ t,
-                          const float* __restrict__ m, int64_t n, int64_t p0, float inv_cnt, float gW2[16],
-                          float& loss_acc) {
+__device__ __forceinline__ void load_params(MlpLds& L, const float* P) {
+  const int tid = threadIdx.x;
+  for (int e = tid; e < kH * kH; e += 256) {
+    const float w = P[OFF_W2 + e];
+    L.W2[e >> 6][e & 63] = w;
+    L.W2T[e & 63][e >> 6] = w;
+  }
+  if (tid < kH) {
+    L.W1[tid] = P[OFF_W1 + tid];
+    L.b1[tid] = P[OFF_B1 + tid];
+    L.b2[tid] = P[OFF_B2 + tid];
+  }
+  for (int e = tid; e < kOut * kH; e += 256) L.W3[e >> 6][e & 63] = P[OFF_W3 + e];
+  if (tid < kOut) L.b3[tid] = P[OFF_B3 + tid];
+}
+
+__device__ __forceinline__ void tile_grad(MlpLds& L, const float* __restrict__ x, const float* __restrict__ t,
+                                          const float* __restrict__ m, int64_t n, int64_t p0, float inv_cnt,
+                                          MlpAcc& G) {
   const int tid = threadIdx.x;
   if (tid < kTile) L.x[tid] = (p0 + tid < n) ? x[p0 + tid] : 0.0f;
   __syncthreads();
   // h1 = tanh(W1 x + b1)
+#pragma unroll
   for (int e = tid; e < kTile * kH; e += 256) {
     const int p = e >> 6, k = e & 63;
-    L.H1[p][k] = tanhf(fmaf(L.P[OFF_W1 + k], L.x[p], L.P[OFF_B1 + k]));
+    const float h = tanhf(fmaf(L.W1[k], L.x[p], L.b1[k]));
+    L.H1[p][k] = h;
+    L.H1T[k][p] = h;
   }
   __syncthreads();
+  const int q0 = 4 * (tid & 15), r0 = 2 * (tid >> 4);  // this thread's 4 features and 2 points
   // h2 = tanh(W2 h1 + b2)
-  for (int e = tid; e < kTile * kH; e += 256) {
-    const int p = e >> 6, j = e & 63;
-    float a = L.P[OFF_B2 + j];
-    const float* w = &L.P[OFF_W2 + j * kH];
-    for (int k = 0; k < kH; ++k) a = fmaf(w[k], L.H1[p][k], a);
-    L.H2[p][j] = tanhf(a);
+  {
+    float a[2][4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) a[0][c] = a[1][c] = L.b2[q0 + c];
+#pragma unroll 8
+    for (int k = 0; k < kH; ++k) {
+      const float4 w = *reinterpret_cast<const float4*>(&L.W2T[k][q0]);
+      const float2 h = *reinterpret_cast<const float2*>(&L.H1T[k][r0]);
+      a[0][0] = fmaf(w.x, h.x, a[0][0]);
+      a[0][1] = fmaf(w.y, h.x, a[0][1]);
+      a[0][2] = fmaf(w.z, h.x, a[0][2]);
+      a[0][3] = fmaf(w.w, h.x, a[0][3]);
+      a[1][0] = fmaf(w.x, h.y, a[1][0]);
+      a[1][1] = fmaf(w.y, h.y, a[1][1]);
+      a[1][2] = fmaf(w.z, h.y, a[1][2]);
+      a[1][3] = fmaf(w.w, h.y, a[1][3]);
+    }
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) L.H2[r0 + r][q0 + c] = tanhf(a[r][c]);
   }
   __syncthreads();
   // y = W3 h2 + b3; masked residual; dL/dy
-  for (int e = tid; e < kTile * kOut; e += 256) {
-    const int p = e / kOut, o = e % kOut;
+  if (tid < kTile * kOut) {
+    const int p = tid / kOut, o = tid % kOut;
     const int64_t q = p0 + p;
-    float a = L.P[OFF_B3 + o];
-    for (int j = 0; j < kH; ++j) a = fmaf(L.P[OFF_W3 + o * kH + j], L.H2[p][j], a);
+    float mk = 0.0f, tg = 0.0f;
+    if (q < n) {
+      mk = m[q * kOut + o];
+      tg = t[q * kOut + o];
+    }
+    float a = L.b3[o];
+#pragma unroll 16
+    for (int j = 0; j < kH; ++j) a = fmaf(L.W3[o][j], L.H2[p][j], a);
     float r = 0.0f;
-    if (q < n) r = m[q * kOut + o] * (a - t[q * kOut + o]);
-    loss_acc = fmaf(r, r, loss_acc);
+    if (q < n) r = mk * (a - tg);
+    G.loss = fmaf(r, r, G.loss);
     L.dy[p][o] = 2.0f * r * inv_cnt;
   }
   __syncthreads();
   // dW3, db3
-  for (int e = tid; e < kOut * kH + kOut; e += 256) {
-    float g = 0.0f;
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int e = tid + 256 * u;
     if (e < kOut * kH) {
-      const int o = e / kH, j = e % kH;
+      const int o = e >> 6, j = e & 63;
+      float g = 0.0f;
+#pragma unroll 8
       for (int p = 0; p < kTile; ++p) g = fmaf(L.dy[p][o], L.H2[p][j], g);
-    } else {
-      const int o = e - kOut * kH;
-      for (int p = 0; p < kTile; ++p) g += L.dy[p][o];
+      G.W3[u] += g;
+    } else if (e - kOut * kH < kOut) {
+      float g = 0.0f;
+      for (int p = 0; p < kTile; ++p) g += L.dy[p][e - kOut * kH];
+      G.b3 += g;
     }
-    L.gsmall[small_idx(OFF_W3 + e)] += g;
   }
   // dz2 = (W3^T dy) (1 - h2^2)
+#pragma unroll
   for (int e = tid; e < kTile * kH; e += 256) {
     const int p = e >> 6, j = e & 63;
     float a = 0.0f;
-    for (int o = 0; o < kOut; ++o) a = fmaf(L.P[OFF_W3 + o * kH + j], L.dy[p][o], a);
+#pragma unroll
+    for (int o = 0; o < kOut; ++o) a = fmaf(L.W3[o][j], L.dy[p][o], a);
     const float h = L.H2[p][j];
-    L.D2[p][j] = a * ((1.0f - h) * (1.0f + h));
+    const float d = a * ((1.0f - h) * (1.0f + h));
+    L.D2[p][j] = d;
+    L.D2T[j][p] = d;
   }
   __syncthreads();
-  // dW2 (registers), db2
+  // dW2, db2
   {
-    const int j = tid >> 2, k0 = (tid & 3) * 16;
+    const int j0 = 4 * (tid >> 4);
+#pragma unroll 4
     for (int p = 0; p < kTile; ++p) {
-      const float d = L.D2[p][j];
+      const float4 d = *reinterpret_cast<const float4*>(&L.D2[p][j0]);
+      const float4 h = *reinterpret_cast<const float4*>(&L.H1[p][q0]);
+      const float dv[4] = {d.x, d.y, d.z, d.w}, hv[4] = {h.x, h.y, h.z, h.w};
 #pragma unroll
-      for (int c = 0; c < 16; ++c) gW2[c] = fmaf(d, L.H1[p][k0 + c], gW2[c]);
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) G.W2[r][c] = fmaf(dv[r], hv[c], G.W2[r][c]);
     }
   }
   if (tid < kH) {
     float g = 0.0f;
+#pragma unroll 8
     for (int p = 0; p < kTile; ++p) g += L.D2[p][tid];
-    L.gsmall[small_idx(OFF_B2 + tid)] += g;
+    G.b2 += g;
   }
-  // dz1 = (W2^T dz2) (1 - h1^2), overwriting H1's slot would race with dW2: use H2's space
-  __syncthreads();
-  for (int e = tid; e < kTile * kH; e += 256) {
-    const int p = e >> 6, k = e & 63;
-    float a = 0.0f;
-    for (int j = 0; j < kH; ++j) a = fmaf(L.P[OFF_W2 + j * kH + k], L.D2[p][j], a);
-    const float h = L.H1[p][k];
-    L.H2[p][k] = a * ((1.0f - h) * (1.0f + h));
+  // dz1 = (W2^T dz2) (1 - h1^2), in H2's place (H2 was last read before the barrier above)
+  {
+    float a[2][4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) a[0][c] = a[1][c] = 0.0f;
+#pragma unroll 8
+    for (int j = 0; j < kH; ++j) {
+      const float4 w = *reinterpret_cast<const float4*>(&L.W2[j][q0]);
+      const float2 d = *reinterpret_cast<const float2*>(&L.D2T[j][r0]);
+      a[0][0] = fmaf(w.x, d.x, a[0][0]);
+      a[0][1] = fmaf(w.y, d.x, a[0][1]);
+      a[0][2] = fmaf(w.z, d.x, a[0][2]);
+      a[0][3] = fmaf(w.w, d.x, a[0][3]);
+      a[1][0] = fmaf(w.x, d.y, a[1][0]);
+      a[1][1] = fmaf(w.y, d.y, a[1][1]);
+      a[1][2] = fmaf(w.z, d.y, a[1][2]);
+      a[1][3] = fmaf(w.w, d.y, a[1][3]);
+    }
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const float h = L.H1[r0 + r][q0 + c];
+        L.H2[r0 + r][q0 + c] = a[r][c] * ((1.0f - h) * (1.0f + h));
+      }
   }
   __syncthreads();
   // dW1, db1
   if (tid < 2 * kH) {
     const int k = tid & 63;
     float g = 0.0f;
-    if (tid < kH)
+    if (tid < kH) {
+#pragma unroll 8
       for (int p = 0; p < kTile; ++p) g = fmaf(L.H2[p][k], L.x[p], g);
-    else
+    } else {
+#pragma unroll 8
       for (int p = 0; p < kTile; ++p) g += L.H2[p][k];
-    L.gsmall[small_idx((tid < kH ? OFF_W1 : OFF_B1) + k)] += g;
+    }
+    G.l1 += g;
   }
   __syncthreads();
 }
 
-// Gradient of the whole data set for the parameters in L.P: blocks take
-// tiles b, b + G, ...; per-block partial gradients go to partial[b][*] and
-// partial losses to ploss[b].
-__device__ void block_grad(MlpLds& L, const MlpArgs& A, float* __restrict__ partial, float* __restrict__ ploss) {
+// Gradient of the whole data set for the parameters in L: blocks take
+// tiles b, b + G, ...; per-block partial gradients go to partial[b][*] (rows
+// of kMlpStride) and partial losses to ploss[b].
+__device__ __forceinline__ void block_grad(MlpLds& L, const MlpArgs& A) {
   const int tid = threadIdx.x;
-  float gW2[16];
-#pragma unroll
-  for (int c = 0; c < 16; ++c) gW2[c] = 0.0f;
-  for (int i = tid; i < kMlpParams - 4096; i += 256) L.gsmall[i] = 0.0f;
-  float loss_acc = 0.0f;
-  __syncthreads();
+  MlpAcc G{};
   const int64_t n_tiles = (A.n + kTile - 1) / kTile;
   for (int64_t tl = blockIdx.x; tl < n_tiles; tl += gridDim.x)
-    tile_grad(L, A.x, A.t, A.mask, A.n, tl * kTile, A.inv_cnt, gW2, loss_acc);
-  float* out = partial + (size_t)blockIdx.x * kMlpParams;
-  const int j = tid >> 2, k0 = (tid & 3) * 16;
+    tile_grad(L, A.x, A.t, A.mask, A.n, tl * kTile, A.inv_cnt, G);
+  float* out = A.partial + (size_t)blockIdx.x * kMlpStride;
+  const int j0 = 4 * (tid >> 4), k0 = 4 * (tid & 15);
 #pragma unroll
-  for (int c = 0; c < 16; ++c) out[OFF_W2 + j * kH + k0 + c] = gW2[c];
-  for (int i = tid; i < kMlpParams - 4096; i += 256) out[i < OFF_W2 ? i : i + 4096] = L.gsmall[i];
-  L.loss[tid] = loss_acc;
+  for (int r = 0; r < 4; ++r)
+    *reinterpret_cast<float4*>(&out[OFF_W2 + (j0 + r) * kH + k0]) =
+        make_float4(G.W2[r][0], G.W2[r][1], G.W2[r][2], G.W2[r][3]);
+  out[OFF_W3 + tid] = G.W3[0];
+  if (tid < kOut * kH - 256)
+    out[OFF_W3 + 256 + tid] = G.W3[1];
+  else if (tid - (kOut * kH - 256) < kOut)
+    out[OFF_B3 + tid - (kOut * kH - 256)] = G.b3;
+  if (tid < kH) out[OFF_B2 + tid] = G.b2;
+  if (tid < 2 * kH) out[(tid < kH ? OFF_W1 : OFF_B1 - kH) + tid] = G.l1;
+  // loss: a fixed tree over the wave, then the waves in turn
+  float s = G.loss;
+  for (int d = 32; d > 0; d >>= 1) s += __shfl_xor(s, d, 64);
+  if ((tid & 63) == 0) L.red[tid >> 6] = s;
   __syncthreads();
-  if (tid == 0) {
-    float s = 0.0f;
-    for (int i = 0; i < 256; ++i) s += L.loss[i];
-    ploss[blockIdx.x] = s;
+  if (tid == 0) A.ploss[blockIdx.x] = (L.red[0] + L.red[1]) + (L.red[2] + L.red[3]);
+}
+
+// Whole block: the sum over the nb partial gradients of the parameters
+// [first, first + per), per = 64, 128 or 256: thread tid (and 256 / per row
+// groups side by side, combined in order) returns parameter first + tid of the
+// first `per` threads.
+__device__ __forceinline__ float reduce_rows(const float* partial, int nb, int first, int per,
+                                             float* red) {
+  const int tid = threadIdx.x, c = tid & (per - 1), grp = tid / per, groups = 256 / per;
+  const int i = first + c;
+  float g = 0.0f;
+  if (i < kMlpParams) {
+#pragma unroll 8
+    for (int b = grp; b < nb; b += groups) g += partial[(size_t)b * kMlpStride + i];
   }
+  __syncthreads();
+  red[tid] = g;
+  __syncthreads();
+  float s = red[c];
+  for (int k = 1; k < groups; ++k) s += red[k * per + c];
+  return s;
+}
+
+// Parameters a block reduces at a time: with enough blocks a few rows groups
+// share the rows of one parameter, so that fewer loads wait on each other.
+__device__ __forceinline__ int reduce_width(int blocks) {
+  return blocks * 64 >= kMlpParams ? 64 : (blocks * 128 >= kMlpParams ? 128 : 256);
 }
 
 __global__ __launch_bounds__(256) void k_mlp_grad(MlpArgs A) {
-  extern __shared__ float smem[];
-  MlpLds& L = *reinterpret_cast<MlpLds*>(smem);
-  for (int i = threadIdx.x; i < kMlpParams; i += 256) L.P[i] = A.params[i];
+  __shared__ MlpLds L;
+  load_params(L, A.params);
   __syncthreads();
-  block_grad(L, A, A.partial, A.ploss);
+  block_grad(L, A);
 }
 
 // Fixed-order reduction of the per-block partials.
-__global__ void k_mlp_reduce(const float* __restrict__ partial, const float* __restrict__ ploss, int nb,
-                             float* __restrict__ grad, float* __restrict__ loss) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < kMlpParams) {
-    float s = 0.0f;
-    for (int b = 0; b < nb; ++b) s += partial[(size_t)b * kMlpParams + i];
-    grad[i] = s;
-  }
-  if (i == 0) {
+__global__ __launch_bounds__(256) void k_mlp_reduce(const float* __restrict__ partial, const float* __restrict__ ploss,
+                                                    int nb, float* __restrict__ grad, float* __restrict__ loss) {
+  __shared__ float red[256];
+  const int first = blockIdx.x * 64;
+  const float g = reduce_rows(partial, nb, first, 64, red);
+  if (threadIdx.x < 64 && first + (int)threadIdx.x < kMlpParams) grad[first + threadIdx.x] = g;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
     float s = 0.0f;
     for (int b = 0; b < nb; ++b) s += ploss[b];
     *loss = s;
@@ -193,38 +307,50 @@ __global__ void k_mlp_reduce(const float* __restrict__ partial, const float* __r
 }
 
 // Every epoch: gradient (all blocks), fixed-order reduction and Adam update
-// (one parameter per thread of the grid), then the blocks reload the
-// parameters.  Two grid barriers per epoch.
+// (the parameters dealt over the blocks), then the blocks reload the
+// parameters.  Two grid barriers per epoch; the barrier's completion sums the
+// loss.
 __global__ __launch_bounds__(256) void k_mlp_train(MlpArgs A) {
-  extern __shared__ float smem[];
-  MlpLds& L = *reinterpret_cast<MlpLds*>(smem);
-  cg::grid_group grid = cg::this_grid();
-  const int gtid = blockIdx.x * 256 + threadIdx.x;
-  const int nthr = gridDim.x * 256;
+  __shared__ MlpLds L;
+  __shared__ uint32_t s_pub[kBarWords];
+  __shared__ float s_rate[3];
+  uint32_t gen = 0;
+  const int per = reduce_width((int)gridDim.x);
   for (int e = 0; e < A.epochs; ++e) {
-    for (int i = threadIdx.x; i < kMlpParams; i += 256) L.P[i] = __hip_atomic_load(
-        &A.params[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    load_params(L, A.params);
+    if (threadIdx.x == 255) {
+      s_rate[0] =
+          (float)(A.lr_min + 0.5 * (A.lr0 - A.lr_min) * (1.0 + cos(3.14159265358979323846 * e / A.epochs)));
+      s_rate[1] = 1.0f / (1.0f - powf(A.beta1, (float)(e + 1)));
+      s_rate[2] = 1.0f / (1.0f - powf(A.beta2, (float)(e + 1)));
+    }
     __syncthreads();
-    block_grad(L, A, A.partial, A.ploss);
-    grid.sync();
-    const float lr = (float)(A.lr_min + 0.5 * (A.lr0 - A.lr_min) * (1.0 + cos(3.14159265358979323846 * e / A.epochs)));
-    const float c1 = 1.0f / (1.0f - powf(A.beta1, (float)(e + 1)));
-    const float c2 = 1.0f / (1.0f - powf(A.beta2, (float)(e + 1)));
-    for (int i = gtid; i < kMlpParams; i += nthr) {
-      float g = 0.0f;
-      for (int b = 0; b < (int)gridDim.x; ++b) g += A.partial[(size_t)b * kMlpParams + i];
-      const float m = A.beta1 * A.m[i] + (1.0f - A.beta1) * g;
-      const float v = A.beta2 * A.v[i] + (1.0f - A.beta2) * g * g;
-      A.m[i] = m;
-      A.v[i] = v;
-      A.params[i] -= lr * (m * c1) / (sqrtf(v * c2) + A.eps);
+    block_grad(L, A);
+    grid_barrier(A.bar, gen, s_pub, [](uint32_t*) {});
+    const float lr = s_rate[0], c1 = s_rate[1], c2 = s_rate[2];
+    for (int first = (int)blockIdx.x * per; first < kMlpParams; first += (int)gridDim.x * per) {
+      const int i = first + (int)threadIdx.x;
+      const bool mine = (int)threadIdx.x < per && i < kMlpParams;
+      const float m0 = mine ? A.m[i] : 0.0f, v0 = mine ? A.v[i] : 0.0f, p0 = mine ? A.params[i] : 0.0f;
+      const float g = reduce_rows(A.partial, (int)gridDim.x, first, per, L.red);
+      if (mine) {
+        const float m = A.beta1 * m0 + (1.0f - A.beta1) * g;
+        const float v = A.beta2 * v0 + (1.0f - A.beta2) * g * g;
+        A.m[i] = m;
+        A.v[i] = v;
+        A.params[i] = p0 - lr * (m * c1) / (sqrtf(v * c2) + A.eps);
+      }
     }
-    if (gtid == 0 && A.loss_hist) {
+    if (blockIdx.x == gridDim.x - 1 && A.loss_hist) {  // the block with the fewest parameters
       float s = 0.0f;
-      for (int b = 0; b < (int)gridDim.x; ++b) s += A.ploss[b];
-      A.loss_hist[e] = s * A.inv_cnt;
+      for (int b = (int)threadIdx.x; b < (int)gridDim.x; b += 256) s += A.ploss[b];
+      for (int d = 32; d > 0; d >>= 1) s += __shfl_xor(s, d, 64);
+      __syncthreads();
+      if ((threadIdx.x & 63) == 0) L.red[threadIdx.x >> 6] = s;
+      __syncthreads();
+      if (threadIdx.x == 0) A.loss_hist[e] = ((L.red[0] + L.red[1]) + (L.red[2] + L.red[3])) * A.inv_cnt;
     }
-    grid.sync();
+    grid_barrier(A.bar, gen, s_pub, [](uint32_t*) {});
   }
 }
 
@@ -408,27 +534,25 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
 }
 
 // ---------------------------------------------------------------------------
-size_t mlp_lds_bytes() { return sizeof(MlpLds); }
-
 hipError_t launch_mlp_grad(const MlpArgs& a, int grid, hipStream_t stream) {
-  hipLaunchKernelGGL(k_mlp_grad, dim3(grid), dim3(256), sizeof(MlpLds), stream, a);
+  hipLaunchKernelGGL(k_mlp_grad, dim3(grid), dim3(256), 0, stream, a);
   return hipGetLastError();
 }
 
 hipError_t launch_mlp_reduce(const float* partial, const float* ploss, int nb, float* grad, float* loss,
                              hipStream_t stream) {
-  hipLaunchKernelGGL(k_mlp_reduce, dim3((kMlpParams + 255) / 256), dim3(256), 0, stream, partial, ploss, nb, grad,
+  hipLaunchKernelGGL(k_mlp_reduce, dim3((kMlpParams + 63) / 64), dim3(256), 0, stream, partial, ploss, nb, grad,
                      loss);
   return hipGetLastError();
 }
 
 hipError_t occupancy_mlp_train(int* blocks_per_cu) {
-  return coresident_blocks((const void*)k_mlp_train, 256, sizeof(MlpLds), blocks_per_cu);
+  return coresident_blocks((const void*)k_mlp_train, 256, 0, blocks_per_cu);
 }
 
 hipError_t launch_mlp_train(const MlpArgs& a, int grid, hipStream_t stream) {
   void* kargs[] = {(void*)&a};
-  return hipLaunchCooperativeKernel((const void*)k_mlp_train, dim3(grid), dim3(256), kargs, sizeof(MlpLds), stream);
+  return hipLaunchCooperativeKernel((const void*)k_mlp_train, dim3(grid), dim3(256), kargs, 0, stream);
 }
 
 hipError_t launch_mlp_infer(const InferArgs& a, int grid, hipStream_t stream) {
