@@ -217,7 +217,7 @@ struct SwarmArgs {
 // Coefficient surrogate (1 -> 64 -> 64 -> 6 perceptron).
 constexpr int kMlpParams = 4678;
 constexpr int kMlpStride = 4736;  // floats per row of partial gradients
-constexpr int kMlpTile = 32;      // points a block takes at a time in training
+constexpr int kMlpTile = 16;      // points a block takes at a time in training
 
 struct MlpArgs {
   float* params;        // [kMlpParams], updated in place by training

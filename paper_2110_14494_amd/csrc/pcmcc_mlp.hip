@@ -3,7 +3,7 @@
 // coefficients (the inputs of the fluid model of arXiv:2110.14494 Sec. 2.2,
 // computed by the swarms of Sec. 2.2.2).
 //
-//  * training (FP32): forward and backward over 32-point tiles held in LDS,
+//  * training (FP32): forward and backward over 16-point tiles held in LDS,
 //    gradients reduced in a fixed order (bit-reproducible), full-batch Adam
 //    with a cosine learning rate; one cooperative launch runs every epoch;
 //  * inference (BF16 weights and activations, FP32 accumulation): the 64x64
@@ -30,19 +30,22 @@ static_assert(OFF_B3 + 6 == kMlpParams, "parameter packing");
 // ---------------------------------------------------------------------------
 // Training: one tile of kTile points through forward and backward.  The three
 // 64-wide products (layer 2, its input gradient, its weight gradient) run on
-// register tiles: a thread holds 2 x 4 (or 4 x 4) outputs and reads its two
+// register tiles: a thread holds kRP x 4 (or 4 x 4) outputs and reads its two
 // operands as vectors from LDS copies laid out so that the lanes of a wave
 // read consecutive words; the operands are therefore kept in both orders.
 // Everything is in a fixed order, so results are reproducible.  Bound by
-// the single-precision multiply-adds of a tile on one compute unit (0.9 us a
-// product for 32 points) and the latencies between them.  A thread per output
+// latency: the stages of a tile depend on each other, and one block a compute
+// unit runs each as a few hundred instructions.  A thread per output
 // reading two LDS words per multiply-add, the layer's weights with all lanes
 // on one bank, and 64-point tiles took 163 us an epoch for 1792 points (28
-// blocks); this takes EPOCH_US us (56 blocks).
+// blocks); 32-point tiles of this form take 33 us (56 blocks, 17.6 us of
+// it the tile, 5.2 the parameters, 9.8 the reduction and two barriers), and
+// 16-point tiles 27 us (112 blocks).
 constexpr int kTile = kMlpTile, kTP = kTile + 4;
+constexpr int kRP = kTile / 16;  // points of a thread's register tile
 struct MlpLds {
-  float W2[kH][kH];    // [j][k]
-  float W2T[kH][kH];   // [k][j]
+  float W2[kH][kH];      // [j][k]
+  float W2T[kH][kH + 4];  // [k][j]
   float H1[kTile][kH];
   float H1T[kH][kTP];  // [k][p]
   float D2[kTile][kH];
@@ -93,27 +96,28 @@ __device__ __forceinline__ void tile_grad(MlpLds& L, const float* __restrict__ x
     L.H1T[k][p] = h;
   }
   __syncthreads();
-  const int q0 = 4 * (tid & 15), r0 = 2 * (tid >> 4);  // this thread's 4 features and 2 points
+  const int q0 = 4 * (tid & 15), r0 = kRP * (tid >> 4);  // this thread's 4 features and kRP points
   // h2 = tanh(W2 h1 + b2)
   {
-    float a[2][4];
+    float a[kRP][4];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) a[0][c] = a[1][c] = L.b2[q0 + c];
-#pragma unroll 8
+    for (int r = 0; r < kRP; ++r)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) a[r][c] = L.b2[q0 + c];
+#pragma unroll 16
     for (int k = 0; k < kH; ++k) {
       const float4 w = *reinterpret_cast<const float4*>(&L.W2T[k][q0]);
-      const float2 h = *reinterpret_cast<const float2*>(&L.H1T[k][r0]);
-      a[0][0] = fmaf(w.x, h.x, a[0][0]);
-      a[0][1] = fmaf(w.y, h.x, a[0][1]);
-      a[0][2] = fmaf(w.z, h.x, a[0][2]);
-      a[0][3] = fmaf(w.w, h.x, a[0][3]);
-      a[1][0] = fmaf(w.x, h.y, a[1][0]);
-      a[1][1] = fmaf(w.y, h.y, a[1][1]);
-      a[1][2] = fmaf(w.z, h.y, a[1][2]);
-      a[1][3] = fmaf(w.w, h.y, a[1][3]);
+#pragma unroll
+      for (int r = 0; r < kRP; ++r) {
+        const float h = L.H1T[k][r0 + r];
+        a[r][0] = fmaf(w.x, h, a[r][0]);
+        a[r][1] = fmaf(w.y, h, a[r][1]);
+        a[r][2] = fmaf(w.z, h, a[r][2]);
+        a[r][3] = fmaf(w.w, h, a[r][3]);
+      }
     }
 #pragma unroll
-    for (int r = 0; r < 2; ++r)
+    for (int r = 0; r < kRP; ++r)
 #pragma unroll
       for (int c = 0; c < 4; ++c) L.H2[r0 + r][q0 + c] = tanhf(a[r][c]);
   }
@@ -187,24 +191,25 @@ __device__ __forceinline__ void tile_grad(MlpLds& L, const float* __restrict__ x
   }
   // dz1 = (W2^T dz2) (1 - h1^2), in H2's place (H2 was last read before the barrier above)
   {
-    float a[2][4];
+    float a[kRP][4];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) a[0][c] = a[1][c] = 0.0f;
-#pragma unroll 8
+    for (int r = 0; r < kRP; ++r)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) a[r][c] = 0.0f;
+#pragma unroll 16
     for (int j = 0; j < kH; ++j) {
       const float4 w = *reinterpret_cast<const float4*>(&L.W2[j][q0]);
-      const float2 d = *reinterpret_cast<const float2*>(&L.D2T[j][r0]);
-      a[0][0] = fmaf(w.x, d.x, a[0][0]);
-      a[0][1] = fmaf(w.y, d.x, a[0][1]);
-      a[0][2] = fmaf(w.z, d.x, a[0][2]);
-      a[0][3] = fmaf(w.w, d.x, a[0][3]);
-      a[1][0] = fmaf(w.x, d.y, a[1][0]);
-      a[1][1] = fmaf(w.y, d.y, a[1][1]);
-      a[1][2] = fmaf(w.z, d.y, a[1][2]);
-      a[1][3] = fmaf(w.w, d.y, a[1][3]);
+#pragma unroll
+      for (int r = 0; r < kRP; ++r) {
+        const float d = L.D2T[j][r0 + r];
+        a[r][0] = fmaf(w.x, d, a[r][0]);
+        a[r][1] = fmaf(w.y, d, a[r][1]);
+        a[r][2] = fmaf(w.z, d, a[r][2]);
+        a[r][3] = fmaf(w.w, d, a[r][3]);
+      }
     }
 #pragma unroll
-    for (int r = 0; r < 2; ++r)
+    for (int r = 0; r < kRP; ++r)
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
         const float h = L.H1[r0 + r][q0 + c];
