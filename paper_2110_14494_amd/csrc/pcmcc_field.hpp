@@ -35,9 +35,10 @@ __device__ __forceinline__ RowPos row_pos(int n_x, int ny) { return row_at(xcd_b
 inline dim3 row_grid(int n_x, int ny, int nz) {
   return dim3((unsigned)((size_t)((n_x + kRowThreads - 1) / kRowThreads) * (size_t)ny * (size_t)nz));
 }
-// The defect pass: kDefectRows consecutive row blocks per block.
-constexpr unsigned kDefectRows = 8;
-inline unsigned defect_blocks(int nx, int ny, int nz) { return (row_grid(nx, ny, nz).x + kDefectRows - 1) / kDefectRows; }
+// Threads per block of the multigrid's item kernels, and the blocks of the
+// defect pass (one partial maximum each).
+constexpr unsigned kMgThreads = 256;
+size_t defect_blocks(int nx, int ny, int nz);
 
 // Self-consistent field: multigrid levels and the time-step selection state.
 constexpr int kMgMaxLevels = 16;
@@ -63,9 +64,8 @@ struct SelState {
 int mg_levels(int nx, int ny, int nz, MgDims* dims);
 hipError_t launch_sc_rhs(const int64_t* np, const int64_t* ne, const int64_t* nn, size_t n, double scale, double* f,
                          unsigned long long* fmax, hipStream_t s);
-hipError_t mg_vcycle(const MgWork& W, int l, hipStream_t s);
+hipError_t launch_cycle(const MgWork& W, hipStream_t s);
 hipError_t launch_defect(const MgWork& W, unsigned long long* rmax, hipStream_t s);
-hipError_t launch_correct(const MgWork& W, hipStream_t s);
 hipError_t launch_extrapolate(double* phi, double* prev, double r, size_t n, hipStream_t s);
 hipError_t launch_sc_field(const float4* Ea, const double* phi, int nx, int ny, int nz, double dx, float4* E,
                            hipStream_t s);

@@ -755,7 +755,6 @@ int mg_iterate(pcmcc_ctx* c, const pcmcc_grid* g, double* phi, double tol, int m
     return PCMCC_OK;
   }
   for (int it = 0;; ++it) {
-    HIP_TRY(c, hipMemsetAsync(c->sc_red + 1, 0, sizeof(unsigned long long), c->stream));
     HIP_TRY(c, launch_defect(c->mg, c->sc_red + 1, c->stream));
     rc = read_red(c, 1, 1);
     if (rc) return rc;
@@ -764,9 +763,7 @@ int mg_iterate(pcmcc_ctx* c, const pcmcc_grid* g, double* phi, double tol, int m
     *cycles = it;
     *rel = rmax / fmax;
     if (*rel <= tol || it >= max_cycles) break;
-    HIP_TRY(c, hipMemsetAsync(c->mg.u[0], 0, ncell * sizeof(float), c->stream));
-    HIP_TRY(c, mg_vcycle(c->mg, 0, c->stream));
-    HIP_TRY(c, launch_correct(c->mg, c->stream));
+    HIP_TRY(c, launch_cycle(c->mg, c->stream));
   }
   return PCMCC_OK;
 }

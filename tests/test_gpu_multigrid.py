@@ -19,6 +19,10 @@ pytestmark = pytest.mark.gpu
     (63, 1, 1),      # the longest side of the direct solve
     (64, 1, 3),      # one more: sweeps
     (80, 48, 112),   # three launched levels above the direct one
+    (32, 32, 32),    # rows of 4 cells of a colour per thread
+    (24, 24, 20),    # rows of 2 (20 / 2 is no multiple of 4)
+    (20, 22, 18),    # rows of 1
+    (22, 34, 30),    # rows of 1, an odd count of them
 ])
 def test_potential_with_any_coarsest_level(shape):
     from paper_2110_14494_amd import pic
@@ -41,3 +45,23 @@ def test_potential_with_any_coarsest_level(shape):
     # side depends on z only and peaks at dx^2 (nz^2 + 1) / 8
     bound = tol * np.max(np.abs(rho)) / F.EPS0 * dx * dx * (nz * nz + 1) / 8
     assert np.max(np.abs(phi.cpu().numpy() - ref)) <= bound + 1e-13 * np.max(np.abs(ref))
+
+
+@pytest.mark.parametrize("nx", [32, 20, 18])
+def test_potential_off_16_bytes(nx):
+    """A potential that starts 8 bytes off a 16-byte boundary gives the same."""
+    from paper_2110_14494_amd import pic
+    shape = (24, 20, nx)
+    rng = np.random.default_rng(nx)
+    dens = [torch.from_numpy(rng.integers(0, 2 ** 40, size=shape, dtype=np.int64)).cuda() for _ in range(3)]
+    grid = pic.DeviceGrid({"E": np.zeros(shape + (4,), np.float32), "x0": 0.0, "y0": 0.0, "z0": 0.0, "dx": 3e-5})
+    n = int(np.prod(shape))
+    print(f"[gpu] unaligned potential {nx}", flush=True)
+    with pic.Context(0) as ctx:
+        out = []
+        for off in (0, 1):
+            phi = torch.zeros(n + 1, dtype=torch.float64, device="cuda")[off:off + n].view(shape)
+            assert phi.data_ptr() % 16 == 8 * off
+            ctx.solve_potential(grid, *dens, phi, tol=1e-10)
+            out.append(phi.clone())
+    assert torch.equal(out[0], out[1])
