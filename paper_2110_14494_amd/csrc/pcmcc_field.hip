@@ -388,6 +388,125 @@ struct MgTailArgs {
   float inv_h2[kMgMaxLevels];
 };
 
+constexpr int kTailThreads = 1024;
+
+// Block-wide barrier, or for a wave on its own the ordering of its LDS
+// accesses alone.
+template <bool kWave>
+__device__ __forceinline__ void tail_sync() {
+  if constexpr (kWave) {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  } else {
+    __syncthreads();
+  }
+}
+
+// `iters` red-black sweeps of a level of even nx, at most two cells of a
+// colour per thread (kWave: one, by one wave).  The neighbours' places, the
+// right-hand side and the reciprocal diagonal of a thread's cells are formed
+// once for all sweeps; a missing neighbour reads `zero`, a word of LDS that
+// holds 0.  x / d is x r, corrected by the exact remainder: the correctly
+// rounded quotient, since r is the rounded 1 / d (Markstein), as the plain
+// division gives.
+template <bool kWave>
+__device__ void tail_sweeps(float* u, const float* f, MgDims d, float h2, int iters, int zero) {
+#pragma clang fp contract(off)
+  constexpr int kR = kWave ? 1 : 2, kN = kWave ? 64 : kTailThreads;
+  const int hx = d.nx >> 1, n = d.nx * d.ny * d.nz, nh = n >> 1, plane = d.nx * d.ny;
+  int at[2][kR], nb[2][kR][6];
+  float hf[2][kR], dg[2][kR], rd[2][kR];
+#pragma unroll
+  for (int color = 0; color < 2; ++color)
+#pragma unroll
+    for (int r = 0; r < kR; ++r) {
+      const int q = (int)threadIdx.x + r * kN;
+      at[color][r] = -1;
+      if (q < nh) {
+        const int row = q / hx, k = row / d.ny, j = row - k * d.ny;
+        const int i = 2 * (q - row * hx) + ((j + k + color) & 1);
+        const int c = row * d.nx + i;
+        at[color][r] = c;
+        nb[color][r][0] = i > 0 ? c - 1 : zero;
+        nb[color][r][1] = i < d.nx - 1 ? c + 1 : zero;
+        nb[color][r][2] = j > 0 ? c - d.nx : zero;
+        nb[color][r][3] = j < d.ny - 1 ? c + d.nx : zero;
+        nb[color][r][4] = k > 0 ? c - plane : zero;
+        nb[color][r][5] = k < d.nz - 1 ? c + plane : zero;
+        hf[color][r] = h2 * f[c];
+        dg[color][r] = diag_at(i, j, k, d.nx, d.ny, d.nz);
+        rd[color][r] = 1.0f / dg[color][r];
+      }
+    }
+  for (int it = 0; it < iters; ++it)
+#pragma unroll
+    for (int color = 0; color < 2; ++color) {
+#pragma unroll
+      for (int r = 0; r < kR; ++r)
+        if (at[color][r] >= 0) {
+          const int* b = nb[color][r];
+          float s = 0.0f;
+          s += u[b[0]];
+          s += u[b[1]];
+          s += u[b[2]];
+          s += u[b[3]];
+          s += u[b[4]];
+          s += u[b[5]];
+          const float x = s - hf[color][r];
+          const float q = x * rd[color][r];
+          u[at[color][r]] = fmaf(fmaf(-dg[color][r], q, x), rd[color][r], q);
+        }
+      tail_sync<kWave>();
+    }
+}
+
+// Residual of level (u, f, d) averaged into the coarse right-hand side fc (red
+// children only, as in k_mg_restrict), the coarse correction cleared.
+template <bool kWave>
+__device__ void tail_restrict(const float* u, const float* f, MgDims d, float inv_h2, float* uc, float* fc) {
+#pragma clang fp contract(off)
+  constexpr int kN = kWave ? 64 : kTailThreads;
+  const int cx = d.nx / 2, cy = d.ny / 2, nc = cx * cy * (d.nz / 2);
+  for (int C = threadIdx.x; C < nc; C += kN) {
+    const int row = C / cx, I = C - row * cx, K = row / cy, J = row - K * cy;
+    float acc = 0.0f;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      if (((q ^ (q >> 1) ^ (q >> 2)) & 1) != 0) continue;
+      const int i = 2 * I + (q & 1), j = 2 * J + ((q >> 1) & 1), k = 2 * K + (q >> 2);
+      float dg;
+      const float s = nb_sum(u, i, j, k, d.nx, d.ny, d.nz, dg);
+      const int c = (k * d.ny + j) * d.nx + i;
+      acc += f[c] - (s - dg * u[c]) * inv_h2;
+    }
+    fc[C] = 0.125f * acc;
+    uc[C] = 0.0f;
+  }
+  tail_sync<kWave>();
+}
+
+// u += trilinear interpolation of the coarse correction, black cells only (as
+// k_mg_prolong).
+template <bool kWave>
+__device__ void tail_prolong(float* u, MgDims d, const float* U) {
+#pragma clang fp contract(off)
+  constexpr int kN = kWave ? 64 : kTailThreads;
+  const int cx = d.nx / 2, cy = d.ny / 2, cz = d.nz / 2, hx = cx, nh = (d.nx * d.ny * d.nz) >> 1;
+  for (int q = threadIdx.x; q < nh; q += kN) {
+    const int row = q / hx, k = row / d.ny, j = row - k * d.ny;
+    const int I = q - row * hx, i = 2 * I + ((j + k + 1) & 1), J = j >> 1, K = k >> 1;
+    const int I2 = I + ((i & 1) ? 1 : -1), J2 = J + ((j & 1) ? 1 : -1), K2 = K + ((k & 1) ? 1 : -1);
+    const float v = 27.0f * coarse_at(U, I, J, K, cx, cy, cz) +
+                    9.0f * (coarse_at(U, I2, J, K, cx, cy, cz) + coarse_at(U, I, J2, K, cx, cy, cz) +
+                            coarse_at(U, I, J, K2, cx, cy, cz)) +
+                    3.0f * (coarse_at(U, I2, J2, K, cx, cy, cz) + coarse_at(U, I2, J, K2, cx, cy, cz) +
+                            coarse_at(U, I, J2, K2, cx, cy, cz)) +
+                    coarse_at(U, I2, J2, K2, cx, cy, cz);
+    u[row * d.nx + i] += v * (1.0f / 64.0f);
+  }
+  tail_sync<kWave>();
+}
+
 __device__ void tail_smooth(float* u, const float* f, MgDims d, float h2, int color) {
 #pragma clang fp contract(off)
   const int n = d.nx * d.ny * d.nz;
@@ -462,10 +581,15 @@ __device__ void tail_direct(float* u, const float* f, MgDims d, float h2, double
   pass(w1, w0, mx, nx, 1, false, [&](double*, int c, double s) { u[c] = (float)s; });
 }
 
-__global__ __launch_bounds__(512) void k_mg_tail(MgTailArgs A) {
+// From the first level of at most 128 cells on (if the coarsest is swept) one
+// wave runs the cycle alone: its LDS accesses need no block barrier, and these
+// levels' half sweeps, 48 of 64 for a 16^3 tail, are a chain of latencies
+// anyway.  16^3 to 2^3: 44 us with a block barrier and fresh index arithmetic for
+// every half sweep and 512 threads, TAIL_US us so.
+__global__ __launch_bounds__(kTailThreads) void k_mg_tail(MgTailArgs A) {
 #pragma clang fp contract(off)
   __shared__ double s_w[2 * kMgCoarseMax + kMgDirectMat];  // direct solve: two work grids, the matrices
-  __shared__ float s_u[kMgTailCells];
+  __shared__ float s_u[kMgTailCells + 1];                  // the last word is zero
   __shared__ float s_f[kMgTailCells];
   __shared__ int off[kMgMaxLevels];  // level offsets in s_u / s_f
   if (threadIdx.x == 0) {
@@ -474,68 +598,55 @@ __global__ __launch_bounds__(512) void k_mg_tail(MgTailArgs A) {
       off[l] = o;
       o += A.d[l].nx * A.d[l].ny * A.d[l].nz;
     }
+    s_u[kMgTailCells] = 0.0f;
   }
   const MgDims d0 = A.d[A.first];
   const int n0 = d0.nx * d0.ny * d0.nz;
-  for (int c = threadIdx.x; c < n0; c += blockDim.x) {
+  for (int c = threadIdx.x; c < n0; c += kTailThreads) {
     s_u[c] = 0.0f;
     s_f[c] = A.f[c];
   }
   __syncthreads();
-  for (int l = A.first; l < A.levels - 1; ++l) {  // down: pre-smoothing, restriction
-    const MgDims d = A.d[l], dc = A.d[l + 1];
-    float *u = s_u + off[l], *uc = s_u + off[l + 1], *fc = s_f + off[l + 1];
-    const float* f = s_f + off[l];
-    for (int it = 0; it < 2; ++it)
-      for (int color = 0; color < 2; ++color) tail_smooth(u, f, d, A.h2[l], color);
-    const int nc = dc.nx * dc.ny * dc.nz;
-    for (int C = threadIdx.x; C < nc; C += blockDim.x) {
-      const int I = C % dc.nx, J = (C / dc.nx) % dc.ny, K = C / (dc.nx * dc.ny);
-      float acc = 0.0f;
-      for (int q = 0; q < 8; ++q) {  // red children only, as in k_mg_restrict
-        if (((q ^ (q >> 1) ^ (q >> 2)) & 1) != 0) continue;
-        const int i = 2 * I + (q & 1), j = 2 * J + ((q >> 1) & 1), k = 2 * K + (q >> 2);
-        float dg;
-        const float s = nb_sum(u, i, j, k, d.nx, d.ny, d.nz, dg);
-        const size_t c = idx3(i, j, k, d.nx, d.ny);
-        acc += f[c] - (s - dg * u[c]) * A.inv_h2[l];
+  const int last = A.levels - 1;
+  auto zero = [&](int l) { return kMgTailCells - off[l]; };  // the zero word, from a level's u
+  int wave = A.levels;                                       // first level that one wave runs
+  if (!A.direct && (A.d[last].nx & 1) == 0)
+    for (wave = A.first; A.d[wave].nx * A.d[wave].ny * A.d[wave].nz > 128 && wave < last;) ++wave;
+  if (wave == last && A.d[last].nx * A.d[last].ny * A.d[last].nz > 128) wave = A.levels;
+  int l = A.first;
+  for (; l < last && l < wave; ++l) {  // down: pre-smoothing, restriction
+    tail_sweeps<false>(s_u + off[l], s_f + off[l], A.d[l], A.h2[l], 2, zero(l));
+    tail_restrict<false>(s_u + off[l], s_f + off[l], A.d[l], A.inv_h2[l], s_u + off[l + 1], s_f + off[l + 1]);
+  }
+  if (l == wave) {
+    if (threadIdx.x < 64) {
+      for (; l < last; ++l) {
+        tail_sweeps<true>(s_u + off[l], s_f + off[l], A.d[l], A.h2[l], 2, zero(l));
+        tail_restrict<true>(s_u + off[l], s_f + off[l], A.d[l], A.inv_h2[l], s_u + off[l + 1], s_f + off[l + 1]);
       }
-      fc[C] = 0.125f * acc;
-      uc[C] = 0.0f;
+      tail_sweeps<true>(s_u + off[last], s_f + off[last], A.d[last], A.h2[last], A.coarse_iters, zero(last));
+      for (l = last - 1; l >= wave; --l) {
+        tail_prolong<true>(s_u + off[l], A.d[l], s_u + off[l + 1]);
+        tail_sweeps<true>(s_u + off[l], s_f + off[l], A.d[l], A.h2[l], 2, zero(l));
+      }
     }
     __syncthreads();
-  }
-  if (A.direct) {
-    const int l = A.levels - 1;
-    tail_direct(s_u + off[l], s_f + off[l], A.d[l], A.h2[l], s_w, s_w + kMgCoarseMax, s_w + 2 * kMgCoarseMax);
+    l = wave - 1;
   } else {
-    const int l = A.levels - 1;
-    for (int it = 0; it < A.coarse_iters; ++it)
-      for (int color = 0; color < 2; ++color) tail_smooth(s_u + off[l], s_f + off[l], A.d[l], A.h2[l], color);
+    if (A.direct)
+      tail_direct(s_u + off[last], s_f + off[last], A.d[last], A.h2[last], s_w, s_w + kMgCoarseMax,
+                  s_w + 2 * kMgCoarseMax);
+    else
+      for (int it = 0; it < A.coarse_iters; ++it)
+        for (int color = 0; color < 2; ++color)
+          tail_smooth(s_u + off[last], s_f + off[last], A.d[last], A.h2[last], color);
+    l = last - 1;
   }
-  for (int l = A.levels - 2; l >= A.first; --l) {  // up: prolongation, post-smoothing
-    const MgDims d = A.d[l], dc = A.d[l + 1];
-    float* u = s_u + off[l];
-    const float* U = s_u + off[l + 1];
-    const int n = d.nx * d.ny * d.nz;
-    for (int c = threadIdx.x; c < n; c += blockDim.x) {
-      const int i = c % d.nx, j = (c / d.nx) % d.ny, k = c / (d.nx * d.ny);
-      const int I = i >> 1, J = j >> 1, K = k >> 1;
-      const int I2 = I + ((i & 1) ? 1 : -1), J2 = J + ((j & 1) ? 1 : -1), K2 = K + ((k & 1) ? 1 : -1);
-      const float v = 27.0f * coarse_at(U, I, J, K, dc.nx, dc.ny, dc.nz) +
-                      9.0f * (coarse_at(U, I2, J, K, dc.nx, dc.ny, dc.nz) + coarse_at(U, I, J2, K, dc.nx, dc.ny, dc.nz) +
-                              coarse_at(U, I, J, K2, dc.nx, dc.ny, dc.nz)) +
-                      3.0f * (coarse_at(U, I2, J2, K, dc.nx, dc.ny, dc.nz) +
-                              coarse_at(U, I2, J, K2, dc.nx, dc.ny, dc.nz) +
-                              coarse_at(U, I, J2, K2, dc.nx, dc.ny, dc.nz)) +
-                      coarse_at(U, I2, J2, K2, dc.nx, dc.ny, dc.nz);
-      u[c] += v * (1.0f / 64.0f);
-    }
-    __syncthreads();
-    for (int it = 0; it < 2; ++it)
-      for (int color = 0; color < 2; ++color) tail_smooth(u, s_f + off[l], d, A.h2[l], color);
+  for (; l >= A.first; --l) {  // up: prolongation, post-smoothing
+    tail_prolong<false>(s_u + off[l], A.d[l], s_u + off[l + 1]);
+    tail_sweeps<false>(s_u + off[l], s_f + off[l], A.d[l], A.h2[l], 2, zero(l));
   }
-  for (int c = threadIdx.x; c < n0; c += blockDim.x) A.u[c] = s_u[c];
+  for (int c = threadIdx.x; c < n0; c += kTailThreads) A.u[c] = s_u[c];
 }
 
 // Defect of the potential, r = rhs - L phi in double precision: stored in
@@ -899,7 +1010,7 @@ static hipError_t mg_vcycle(const MgWork& W, int l, hipStream_t s) {
     // for a side too long for the matrices in LDS.
     A.direct = m > 2 && dl.nx * dl.nx + dl.ny * dl.ny + dl.nz * dl.nz <= kMgDirectMat;
     if (cells > (size_t)kMgTailCells) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_mg_tail, dim3(1), dim3(512), 0, s, A);
+    hipLaunchKernelGGL(k_mg_tail, dim3(1), dim3(kTailThreads), 0, s, A);
     return hipGetLastError();
   }
   const MgDims dc = W.dims[l + 1];
