@@ -572,7 +572,7 @@ int pcmcc_deposit(pcmcc_ctx* ctx, const float* x, const float* y, const float* z
  * allocate device memory (code being captured into a graph, tight serving
  * loops, harnesses that forbid allocation): the same arguments, result and
  * errors, but the call allocates nothing.  Its scratch is one file-scope
- * device array per GPU (about 50 MiB, held until the process ends) that every
+ * device array per GPU (about 34 MiB, held until the process ends) that every
  * call on that GPU shares, so calls that overlap on one GPU race.  Limits:
  * at most 2^21 particles and 2^18 tiles of 8^3 cells (a 512^3 grid); beyond
  * them PCMCC_EINVAL and rho is untouched.  Synchronises the stream. */

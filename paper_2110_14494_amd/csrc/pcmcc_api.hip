@@ -66,7 +66,6 @@ int pcmcc_destroy(pcmcc_ctx* c) {
   dfree(c->fpack);
   dfree(c->dep.tile_count);
   dfree(c->dep.tile_start);
-  dfree(c->dep.dump);
   dfree(c->dep.sorted);
   dfree(c->wt.cls);
   dfree(c->wt.idx0);

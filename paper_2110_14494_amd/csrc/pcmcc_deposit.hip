@@ -18,7 +18,8 @@
 //  * direct: one thread per particle, 8 global int64 atomics;
 //  * binned (large inputs): the grid is cut into tiles of 8^3 cells, the
 //    particles are counted per tile (per-block LDS hash of tiles, one global
-//    atomic per block and tile), scattered into tile order, and then summed
+//    atomic per block and tile), scattered into tile order (a block reserves
+//    its place in each of its tiles with one atomic), and then summed
 //    per tile in an LDS int64 buffer of 9^3 cells (the tile plus its upper
 //    neighbour layer) that is flushed once per block and tile.  Global
 //    atomics drop from 8 per particle to about 8 per thousand particles in
@@ -35,8 +36,12 @@ namespace pcmcc {
 constexpr int kTile = 8;                                // cells per tile edge
 constexpr int kTileBuf = kTile + 1;                     // with the upper neighbour layer
 constexpr int kTileCells = kTileBuf * kTileBuf * kTileBuf;
-constexpr int kBinRange = 4096;                         // particles per block, count and scatter
-constexpr int kBinHash = 4096;                          // hash entries per block (>= distinct tiles)
+constexpr int kBinThreads = 1024;
+constexpr int kBinPer = 8;                              // particles per thread, count and scatter
+constexpr int kBinRange = kBinThreads * kBinPer;        // particles per block
+constexpr int kSortPer = 16;                            // particles per thread of the particle sort
+constexpr int kSortRange = kBinThreads * kSortPer;
+constexpr int kScanTile = 4096;                         // tile counts per block of the prefix sum
 constexpr int kAccRange = 32768;                        // sorted particles per block, accumulation
 constexpr uint32_t kEmpty = 0xFFFFFFFFu;
 
@@ -128,137 +133,268 @@ __device__ __forceinline__ uint32_t tile_of(const TileGeom& T, float x, float y,
   return ((uint32_t)k * T.ty + j) * T.tx + i;
 }
 
-__device__ __forceinline__ uint32_t tile_hash(uint32_t t) { return (t * 2654435761u) >> 20; }  // 12 bits
+// A block's table of tiles in LDS: open addressing over N = 2^k entries, at
+// least as many as the block has particles, so it never fills.
+template <int N>
+struct TileTable {
+  uint32_t key[N];
+  uint32_t cnt[N];
+};
 
-// Slot of tile t in the block's table, inserting it if new.  The table has
-// at least as many entries as the block has particles, so it never fills.
-__device__ __forceinline__ int hash_insert(uint32_t* keys, uint32_t t) {
-  uint32_t h = tile_hash(t);
+template <int N>
+__device__ __forceinline__ void table_clear(TileTable<N>& H) {
+  for (int e = threadIdx.x; e < N; e += kBinThreads) {
+    H.key[e] = kEmpty;
+    H.cnt[e] = 0;
+  }
+}
+
+// Entry of tile t, inserting it if new.
+template <int N>
+__device__ __forceinline__ uint32_t table_insert(TileTable<N>& H, uint32_t t) {
+  uint32_t h = (t * 2654435761u) >> (32 - __builtin_ctz(N));
   for (;;) {
-    const uint32_t old = atomicCAS(&keys[h], kEmpty, t);
-    if (old == kEmpty || old == t) return (int)h;
-    h = (h + 1) & (kBinHash - 1);
+    const uint32_t old = atomicCAS(&H.key[h], kEmpty, t);
+    if (old == kEmpty || old == t) return h;
+    h = (h + 1) & (N - 1);
   }
 }
 
-// Slot of tile t, which the counting pass inserted (bounded probe; -1 only
-// if it is absent, which the identical tile computation of both passes rules
-// out).
-__device__ __forceinline__ int hash_find(const uint32_t* keys, uint32_t t) {
-  uint32_t h = tile_hash(t);
-  for (int probe = 0; probe < kBinHash; ++probe) {
-    if (keys[h] == t) return (int)h;
-    h = (h + 1) & (kBinHash - 1);
+// Counts tile t in (lanes with `valid`); returns the particle's entry and its
+// number within it.  Where many lanes hold the first lane's tile (particles
+// that come in tile order), they take one insertion and one addition
+// together: 64 lanes on one LDS word are served one after the other.
+template <int N>
+__device__ __forceinline__ uint2 table_count(TileTable<N>& H, uint32_t t, bool valid) {
+  const uint64_t act = __ballot(valid);
+  if (act == 0) return make_uint2(0u, 0u);
+  const int lane = (int)__lane_id(), lead = __ffsll((unsigned long long)act) - 1;
+  const uint32_t t0 = (uint32_t)__builtin_amdgcn_readlane((int)t, lead);
+  const uint64_t same = __ballot(valid && t == t0);
+  uint2 r = make_uint2(0u, 0u);
+  if (__popcll(same) >= 8) {
+    if (lane == lead) {
+      r.x = table_insert(H, t0);
+      r.y = atomicAdd(&H.cnt[r.x], (uint32_t)__popcll(same));
+    }
+    const uint32_t e = (uint32_t)__builtin_amdgcn_readlane((int)r.x, lead);
+    const uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)r.y, lead);
+    r = make_uint2(e, b + __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u)));
+    valid = valid && !((same >> lane) & 1);
   }
-  return -1;
+  if (valid) {
+    const uint32_t e = table_insert(H, t);
+    r = make_uint2(e, atomicAdd(&H.cnt[e], 1u));
+  }
+  return r;
 }
 
-// Pass 1: particles per tile.  Block b covers particles
-// [b kBinRange, (b+1) kBinRange) and records, per tile, its offset within the
-// tile (the value of the tile's counter when it added its count).
-__global__ __launch_bounds__(256) void k_dep_count(const float* __restrict__ x, const float* __restrict__ y,
-                                                    const float* __restrict__ z, uint64_t n, TileGeom T,
-                                                    uint32_t* __restrict__ tile_count, uint2* __restrict__ dump) {
-  __shared__ uint32_t keys[kBinHash];
-  __shared__ uint32_t cnt[kBinHash];
-  for (int e = threadIdx.x; e < kBinHash; e += blockDim.x) {
-    keys[e] = kEmpty;
-    cnt[e] = 0;
+// Pass 1: particles per tile; block b covers [b kBinRange, (b + 1) kBinRange).
+__global__ __launch_bounds__(kBinThreads) void k_dep_count(const float* __restrict__ x, const float* __restrict__ y,
+                                                           const float* __restrict__ z, uint64_t n, TileGeom T,
+                                                           uint32_t* __restrict__ tile_count) {
+  __shared__ TileTable<kBinRange> H;
+  table_clear(H);
+  __syncthreads();
+  const uint64_t p0 = (uint64_t)blockIdx.x * kBinRange + threadIdx.x;
+#pragma unroll 2
+  for (int q = 0; q < kBinPer; ++q) {
+    const uint64_t p = p0 + (uint64_t)q * kBinThreads;
+    const bool valid = p < n;
+    (void)table_count(H, valid ? tile_of(T, x[p], y[p], z[p]) : 0u, valid);
   }
   __syncthreads();
-  const uint64_t p0 = (uint64_t)blockIdx.x * kBinRange;
-  const uint64_t p1 = p0 + kBinRange < n ? p0 + kBinRange : n;
-  for (uint64_t p = p0 + threadIdx.x; p < p1; p += blockDim.x) {
-    const int e = hash_insert(keys, tile_of(T, x[p], y[p], z[p]));
-    atomicAdd(&cnt[e], 1u);
-  }
-  __syncthreads();
-  uint2* d = dump + (size_t)blockIdx.x * kBinHash;
-  for (int e = threadIdx.x; e < kBinHash; e += blockDim.x) {
-    const uint32_t t = keys[e];
-    d[e] = t == kEmpty ? make_uint2(kEmpty, 0u) : make_uint2(t, atomicAdd(&tile_count[t], cnt[e]));
-  }
+  for (int e = threadIdx.x; e < kBinRange; e += kBinThreads)
+    if (H.key[e] != kEmpty) atomicAdd(&tile_count[H.key[e]], H.cnt[e]);
 }
 
-// Exclusive prefix sum of the tile counts (one block): start[t], and
-// start[n_tiles] = total.
-__global__ __launch_bounds__(1024) void k_dep_scan(const uint32_t* __restrict__ count, uint32_t n_tiles,
-                                                    uint32_t* __restrict__ start) {
-  __shared__ uint32_t part[1024];
-  const uint32_t per = (n_tiles + blockDim.x - 1) / blockDim.x;
-  const uint32_t a = threadIdx.x * per, b = min(a + per, n_tiles);
+// Exclusive prefix sum of the tile counts: start[t] and start[n_tiles] = the
+// total; the counts become the tiles' write positions (equal to start).  Two
+// launches: sums of kScanTile counts each, then every block adds the sums
+// before its own (one block for 2^18 tiles took 445 us, these two 8).
+__global__ __launch_bounds__(kBinThreads) void k_dep_sums(const uint32_t* __restrict__ count, uint32_t n_tiles,
+                                                          uint32_t* __restrict__ sums) {
+  __shared__ uint32_t s_w[kBinThreads / 64];
+  const uint32_t a = blockIdx.x * kScanTile + threadIdx.x * 4;
   uint32_t s = 0;
-  for (uint32_t t = a; t < b; ++t) s += count[t];
-  part[threadIdx.x] = s;
+  for (uint32_t t = a; t < a + 4; ++t) s += t < n_tiles ? count[t] : 0u;
+  for (int d = 32; d > 0; d >>= 1) s += __shfl_xor(s, d, 64);
+  if ((threadIdx.x & 63) == 0) s_w[threadIdx.x >> 6] = s;
   __syncthreads();
-  for (uint32_t off = 1; off < blockDim.x; off <<= 1) {
-    const uint32_t v = threadIdx.x >= off ? part[threadIdx.x - off] : 0u;
-    __syncthreads();
-    part[threadIdx.x] += v;
-    __syncthreads();
+  if (threadIdx.x == 0) {
+    uint32_t t = 0;
+    for (int w = 0; w < kBinThreads / 64; ++w) t += s_w[w];
+    sums[blockIdx.x] = t;
   }
-  uint32_t run = part[threadIdx.x] - s;
-  for (uint32_t t = a; t < b; ++t) {
-    start[t] = run;
-    run += count[t];
-  }
-  if (threadIdx.x == blockDim.x - 1) start[n_tiles] = part[threadIdx.x];
 }
 
-// Pass 2: scatter (x, y, z, w) into tile order.
-__global__ __launch_bounds__(256) void k_dep_scatter(const float* __restrict__ x, const float* __restrict__ y,
-                                                      const float* __restrict__ z, const float* __restrict__ w,
-                                                      uint64_t n, TileGeom T, const uint32_t* __restrict__ start,
-                                                      const uint2* __restrict__ dump, float4* __restrict__ sorted) {
-  __shared__ uint32_t keys[kBinHash];
-  __shared__ uint32_t next[kBinHash];
-  const uint2* d = dump + (size_t)blockIdx.x * kBinHash;
-  for (int e = threadIdx.x; e < kBinHash; e += blockDim.x) {
-    const uint2 v = d[e];
-    keys[e] = v.x;
-    next[e] = v.x == kEmpty ? 0u : start[v.x] + v.y;
+__global__ __launch_bounds__(kBinThreads) void k_dep_scan(uint32_t* __restrict__ count, uint32_t n_tiles,
+                                                          const uint32_t* __restrict__ sums,
+                                                          uint32_t* __restrict__ start) {
+  __shared__ uint32_t s_w[kBinThreads / 64], s_before;
+  const int lane = (int)__lane_id(), wave = (int)(threadIdx.x >> 6);
+  uint32_t b = 0;
+  for (uint32_t q = threadIdx.x; q < blockIdx.x; q += kBinThreads) b += sums[q];
+  for (int d = 32; d > 0; d >>= 1) b += __shfl_xor(b, d, 64);
+  if (lane == 0) s_w[wave] = b;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint32_t t = 0;
+    for (int w = 0; w < kBinThreads / 64; ++w) t += s_w[w];
+    s_before = t;
   }
   __syncthreads();
-  const uint64_t p0 = (uint64_t)blockIdx.x * kBinRange;
-  const uint64_t p1 = p0 + kBinRange < n ? p0 + kBinRange : n;
-  for (uint64_t p = p0 + threadIdx.x; p < p1; p += blockDim.x) {
-    const float px = x[p], py = y[p], pz = z[p];
-    const int e = hash_find(keys, tile_of(T, px, py, pz));
-    if (e >= 0) sorted[atomicAdd(&next[e], 1u)] = make_float4(px, py, pz, w[p]);
+  const uint32_t a = blockIdx.x * kScanTile + threadIdx.x * 4;
+  uint32_t c[4], s = 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    c[q] = a + q < n_tiles ? count[a + q] : 0u;
+    s += c[q];
   }
+  uint32_t incl = s;
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t o = __shfl_up(incl, d, 64);
+    if (lane >= d) incl += o;
+  }
+  if (lane == 63) s_w[wave] = incl;
+  __syncthreads();
+  uint32_t run = s_before + incl - s;
+  for (int w = 0; w < wave; ++w) run += s_w[w];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    if (a + q < n_tiles) {
+      start[a + q] = run;
+      count[a + q] = run;
+      run += c[q];
+      if (a + q == n_tiles - 1) start[n_tiles] = run;
+    }
+  }
+}
+
+// Pass 2: scatter (x, y, z, w) into tile order.  pos: the tiles' write
+// positions, advanced by each block by its particles of the tile.
+__global__ __launch_bounds__(kBinThreads) void k_dep_scatter(const float* __restrict__ x, const float* __restrict__ y,
+                                                             const float* __restrict__ z, const float* __restrict__ w,
+                                                             uint64_t n, TileGeom T, uint32_t* __restrict__ pos,
+                                                             float4* __restrict__ sorted) {
+  __shared__ TileTable<kBinRange> H;
+  table_clear(H);
+  __syncthreads();
+  const uint64_t p0 = (uint64_t)blockIdx.x * kBinRange + threadIdx.x;
+  float4 v[kBinPer];
+  uint2 er[kBinPer];
+#pragma unroll
+  for (int q = 0; q < kBinPer; ++q) {
+    const uint64_t p = p0 + (uint64_t)q * kBinThreads;
+    const bool valid = p < n;
+    v[q] = valid ? make_float4(x[p], y[p], z[p], w[p]) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    er[q] = table_count(H, valid ? tile_of(T, v[q].x, v[q].y, v[q].z) : 0u, valid);
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < kBinRange; e += kBinThreads)
+    if (H.key[e] != kEmpty) H.cnt[e] = atomicAdd(&pos[H.key[e]], H.cnt[e]);
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < kBinPer; ++q)
+    if (p0 + (uint64_t)q * kBinThreads < n) sorted[H.cnt[er[q].x] + er[q].y] = v[q];
 }
 
 // Particle sort by tile (the step loop's start order): the count and scan
 // passes above, then every array of a particle moved to its tile's range.
 // Within a tile the order follows the atomics and is not fixed.
-__global__ __launch_bounds__(256) void k_sort_scatter(Soa src, uint64_t n, TileGeom T,
-                                                       const uint32_t* __restrict__ start,
-                                                       const uint2* __restrict__ dump, Soa dst) {
-  __shared__ uint32_t keys[kBinHash];
-  __shared__ uint32_t next[kBinHash];
-  const uint2* d = dump + (size_t)blockIdx.x * kBinHash;
-  for (int e = threadIdx.x; e < kBinHash; e += blockDim.x) {
-    const uint2 v = d[e];
-    keys[e] = v.x;
-    next[e] = v.x == kEmpty ? 0u : start[v.x] + v.y;
+//
+// A block brings its 2^14 particles into tile order in LDS, one array after
+// the other, and writes them from there, so that the particles a block has of
+// one tile leave as one run of consecutive words (12 particles of an
+// unordered streamer head on 512^3 cells).  Each lane writing its own
+// particle's eight words from a block of 2^12 left a partly written line per
+// word: 8.6 ms for 2^26 particles (72 bytes each: 0.9 ms at the HBM rate),
+// 2.5 ms so.
+struct SortLds {
+  union {
+    TileTable<kSortRange> H;
+    struct {
+      uint32_t val[kSortRange];
+      uint32_t dst[kSortRange];
+    } out;
+  };
+  uint32_t wave_sum[kBinThreads / 64];
+};
+
+__global__ __launch_bounds__(kBinThreads) void k_sort_scatter(Soa src, uint64_t n, TileGeom T,
+                                                              uint32_t* __restrict__ pos, Soa dst) {
+  __shared__ SortLds S;
+  table_clear(S.H);
+  __syncthreads();
+  const uint64_t b0 = (uint64_t)blockIdx.x * kSortRange, p0 = b0 + threadIdx.x;
+  const uint32_t m = (uint32_t)(n - b0 < (uint64_t)kSortRange ? n - b0 : (uint64_t)kSortRange);
+  uint2 er[kSortPer];
+#pragma unroll
+  for (int q = 0; q < kSortPer; ++q) {
+    const uint64_t p = p0 + (uint64_t)q * kBinThreads;
+    const bool valid = p < n;
+    er[q] = table_count(S.H, valid ? tile_of(T, src.x[p], src.y[p], src.z[p]) : 0u, valid);
   }
   __syncthreads();
-  const uint64_t p0 = (uint64_t)blockIdx.x * kBinRange;
-  const uint64_t p1 = p0 + kBinRange < n ? p0 + kBinRange : n;
-  for (uint64_t p = p0 + threadIdx.x; p < p1; p += blockDim.x) {
-    const float px = src.x[p], py = src.y[p], pz = src.z[p];
-    const int e = hash_find(keys, tile_of(T, px, py, pz));
-    if (e < 0) continue;  // never: both passes compute the same tile
-    const uint32_t q = atomicAdd(&next[e], 1u);
-    dst.x[q] = px;
-    dst.y[q] = py;
-    dst.z[q] = pz;
-    dst.vx[q] = src.vx[p];
-    dst.vy[q] = src.vy[p];
-    dst.vz[q] = src.vz[p];
-    dst.w[q] = src.w[p];
-    dst.id[q] = src.id[p];
+  // the entries' first ranks in the block (in table order) and their places in
+  // the tiles' ranges
+  const int lane = (int)__lane_id(), wave = (int)(threadIdx.x >> 6);
+  const int e0 = (int)threadIdx.x * kSortPer;
+  uint32_t sum = 0;
+#pragma unroll
+  for (int q = 0; q < kSortPer; ++q) sum += S.H.cnt[e0 + q];
+  uint32_t incl = sum;
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t o = __shfl_up(incl, d, 64);
+    if (lane >= d) incl += o;
   }
+  if (lane == 63) S.wave_sum[wave] = incl;
+  __syncthreads();
+  uint32_t run = incl - sum;
+  for (int w = 0; w < wave; ++w) run += S.wave_sum[w];
+#pragma unroll 4
+  for (int q = 0; q < kSortPer; ++q) {
+    const uint32_t t = S.H.key[e0 + q], c = S.H.cnt[e0 + q];
+    if (t != kEmpty) {
+      S.H.key[e0 + q] = atomicAdd(&pos[t], c);
+      S.H.cnt[e0 + q] = run;
+      run += c;
+    }
+  }
+  __syncthreads();
+  // each particle's rank in the block and its destination
+  uint32_t rank[kSortPer], to[kSortPer];
+#pragma unroll
+  for (int q = 0; q < kSortPer; ++q) {
+    rank[q] = S.H.cnt[er[q].x] + er[q].y;
+    to[q] = S.H.key[er[q].x] + er[q].y;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < kSortPer; ++q)
+    if (p0 + (uint64_t)q * kBinThreads < n) S.out.dst[rank[q]] = to[q];
+  // one 4-byte array at a time (an id's two halves likewise)
+  auto move = [&](const uint32_t* from, uint32_t* into, int stride, int half) {
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kSortPer; ++q) {
+      const uint64_t p = p0 + (uint64_t)q * kBinThreads;
+      if (p < n) S.out.val[rank[q]] = from[p * stride + half];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kSortPer; ++q) {
+      const uint32_t r = threadIdx.x + q * kBinThreads;
+      if (r < m) into[(size_t)S.out.dst[r] * stride + half] = S.out.val[r];
+    }
+  };
+  const float* const f[7] = {src.x, src.y, src.z, src.vx, src.vy, src.vz, src.w};
+  float* const t[7] = {dst.x, dst.y, dst.z, dst.vx, dst.vy, dst.vz, dst.w};
+#pragma unroll 1
+  for (int a = 0; a < 7; ++a)
+    move(reinterpret_cast<const uint32_t*>(f[a]), reinterpret_cast<uint32_t*>(t[a]), 1, 0);
+#pragma unroll 1
+  for (int h = 0; h < 2; ++h) move(reinterpret_cast<const uint32_t*>(src.id), reinterpret_cast<uint32_t*>(dst.id), 2, h);
 }
 
 // One tile run [cur, e) of sorted particles into the LDS buffer of the tile
@@ -379,15 +515,15 @@ DepositNeeds deposit_needs(const DepositGeom& g, uint64_t n) {
   const uint64_t tx = ((uint64_t)g.nx + kTile - 1) / kTile, ty = ((uint64_t)g.ny + kTile - 1) / kTile,
                  tz = ((uint64_t)g.nz + kTile - 1) / kTile;
   d.n_tiles = tx * ty * tz;
-  d.dump_entries = ((n + kBinRange - 1) / kBinRange) * kBinHash;
+  d.scan_sums = (d.n_tiles + kScanTile - 1) / kScanTile;
   d.sorted = n;
   return d;
 }
 
-hipError_t launch_sort_tiles(const Soa& src, uint64_t n, const DepositGeom& g, const DepositWork& W, const Soa& dst,
-                             hipStream_t stream) {
-  if (n == 0) return hipSuccess;
-  TileGeom T;
+// Tile geometry of g, the particles of (x, y, z) counted per tile and the
+// counts turned into starts and write positions.
+static hipError_t count_tiles(const float* x, const float* y, const float* z, uint64_t n, const DepositGeom& g,
+                              const DepositWork& W, TileGeom& T, hipStream_t stream) {
   T.g = g;
   T.tx = (g.nx + kTile - 1) / kTile;
   T.ty = (g.ny + kTile - 1) / kTile;
@@ -395,11 +531,22 @@ hipError_t launch_sort_tiles(const Soa& src, uint64_t n, const DepositGeom& g, c
   const uint32_t n_tiles = (uint32_t)T.tx * T.ty * T.tz;
   hipError_t e = launch_fill_u32(W.tile_count, n_tiles, 0u, stream);
   if (e != hipSuccess) return e;
-  const uint64_t nb = (n + kBinRange - 1) / kBinRange;
-  hipLaunchKernelGGL(k_dep_count, dim3((unsigned)nb), dim3(256), 0, stream, src.x, src.y, src.z, n, T, W.tile_count,
-                     W.dump);
-  hipLaunchKernelGGL(k_dep_scan, dim3(1), dim3(1024), 0, stream, W.tile_count, n_tiles, W.tile_start);
-  hipLaunchKernelGGL(k_sort_scatter, dim3((unsigned)nb), dim3(256), 0, stream, src, n, T, W.tile_start, W.dump, dst);
+  const dim3 nb((unsigned)((n + kBinRange - 1) / kBinRange)), ns((n_tiles + kScanTile - 1) / kScanTile);
+  hipLaunchKernelGGL(k_dep_count, nb, dim3(kBinThreads), 0, stream, x, y, z, n, T, W.tile_count);
+  hipLaunchKernelGGL(k_dep_sums, ns, dim3(kBinThreads), 0, stream, W.tile_count, n_tiles, W.tile_start + n_tiles + 1);
+  hipLaunchKernelGGL(k_dep_scan, ns, dim3(kBinThreads), 0, stream, W.tile_count, n_tiles, W.tile_start + n_tiles + 1,
+                     W.tile_start);
+  return hipGetLastError();
+}
+
+hipError_t launch_sort_tiles(const Soa& src, uint64_t n, const DepositGeom& g, const DepositWork& W, const Soa& dst,
+                             hipStream_t stream) {
+  if (n == 0) return hipSuccess;
+  TileGeom T;
+  const hipError_t e = count_tiles(src.x, src.y, src.z, n, g, W, T, stream);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_sort_scatter, dim3((unsigned)((n + kSortRange - 1) / kSortRange)), dim3(kBinThreads), 0, stream,
+                     src, n, T, W.tile_count, dst);
   return hipGetLastError();
 }
 
@@ -407,18 +554,10 @@ hipError_t launch_deposit_binned(const float* x, const float* y, const float* z,
                                  const DepositGeom& g, int64_t* rho, const DepositWork& W, hipStream_t stream) {
   if (n == 0) return hipSuccess;
   TileGeom T;
-  T.g = g;
-  T.tx = (g.nx + kTile - 1) / kTile;
-  T.ty = (g.ny + kTile - 1) / kTile;
-  T.tz = (g.nz + kTile - 1) / kTile;
-  const uint32_t n_tiles = (uint32_t)T.tx * T.ty * T.tz;
-  hipError_t e = launch_fill_u32(W.tile_count, n_tiles, 0u, stream);
+  const hipError_t e = count_tiles(x, y, z, n, g, W, T, stream);
   if (e != hipSuccess) return e;
-  const uint64_t nb = (n + kBinRange - 1) / kBinRange;
-  hipLaunchKernelGGL(k_dep_count, dim3((unsigned)nb), dim3(256), 0, stream, x, y, z, n, T, W.tile_count, W.dump);
-  hipLaunchKernelGGL(k_dep_scan, dim3(1), dim3(1024), 0, stream, W.tile_count, n_tiles, W.tile_start);
-  hipLaunchKernelGGL(k_dep_scatter, dim3((unsigned)nb), dim3(256), 0, stream, x, y, z, w, n, T, W.tile_start, W.dump,
-                     W.sorted);
+  hipLaunchKernelGGL(k_dep_scatter, dim3((unsigned)((n + kBinRange - 1) / kBinRange)), dim3(kBinThreads), 0, stream, x,
+                     y, z, w, n, T, W.tile_count, W.sorted);
   const uint64_t na = (n + kAccRange - 1) / kAccRange;
   hipLaunchKernelGGL(k_dep_accum, dim3((unsigned)na), dim3(256), 0, stream, W.sorted, n, T, W.tile_start,
                      (unsigned long long*)rho);

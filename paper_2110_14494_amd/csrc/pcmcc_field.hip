@@ -585,7 +585,7 @@ __device__ void tail_direct(float* u, const float* f, MgDims d, float h2, double
 // wave runs the cycle alone: its LDS accesses need no block barrier, and these
 // levels' half sweeps, 48 of 64 for a 16^3 tail, are a chain of latencies
 // anyway.  16^3 to 2^3: 44 us with a block barrier and fresh index arithmetic for
-// every half sweep and 512 threads, TAIL_US us so.
+// every half sweep and 512 threads, 26 us so.
 __global__ __launch_bounds__(kTailThreads) void k_mg_tail(MgTailArgs A) {
 #pragma clang fp contract(off)
   __shared__ double s_w[2 * kMgCoarseMax + kMgDirectMat];  // direct solve: two work grids, the matrices

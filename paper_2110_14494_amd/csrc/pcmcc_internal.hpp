@@ -122,12 +122,11 @@ struct DepositGeom {
 constexpr uint64_t kDepositBinnedMin = 1u << 18;
 struct DepositNeeds {
   bool binned;
-  uint64_t n_tiles, dump_entries, sorted;
+  uint64_t n_tiles, scan_sums, sorted;
 };
 struct DepositWork {
-  uint32_t* tile_count;  // [n_tiles]
-  uint32_t* tile_start;  // [n_tiles + 1]
-  uint2* dump;           // [dump_entries]
+  uint32_t* tile_count;  // [n_tiles] counts, then write positions
+  uint32_t* tile_start;  // [n_tiles + 1], then scan_sums block sums
   float4* sorted;        // [n]
 };
 
@@ -288,7 +287,7 @@ hipError_t launch_deposit(const float* x, const float* y, const float* z, const 
                           const DepositGeom& g, int64_t* rho, hipStream_t stream);
 hipError_t launch_fill_u32(uint32_t* p, uint64_t n, uint32_t v, hipStream_t stream);
 // Sorts n particles of src into dst by deposit tile (8^3 cells, clamped to
-// the grid); needs W's tile counts, starts and dump as the binned deposit.
+// the grid); needs W's tile counts and starts as the binned deposit.
 hipError_t launch_sort_tiles(const Soa& src, uint64_t n, const DepositGeom& g, const DepositWork& W, const Soa& dst,
                              hipStream_t stream);
 hipError_t launch_field_bounds(const float4* E, int nx, int ny, int nz, float2* out, unsigned* emax_bits,

@@ -1,11 +1,11 @@
 // The allocation-free charge deposit (pcmcc_deposit_noalloc): the same
 // fixed-point CIC deposit as pcmcc_deposit, with the binned schedule's
-// scratch (tile counts and starts, per-block tile tables, the tile-ordered
-// particle copy, the range flag) carved out of one file-scope device array
+// scratch (tile counts and starts, the tile-ordered particle copy, the range
+// flag) carved out of one file-scope device array
 // instead of library allocations, for callers that cannot allocate.
 //
 // Every GPU the library runs on holds its own copy of `scratch` (about
-// 50 MiB) until the process ends.  Host code never passes the array's name to
+// 34 MiB) until the process ends.  Host code never passes the array's name to
 // a kernel or a copy: there the name is a host-side stand-in, not a device
 // address.  The device address of each GPU's copy is looked up once, at
 // context creation with that device current (noalloc_setup), and kept per
@@ -22,13 +22,12 @@ constexpr uint64_t kNoallocMaxParticles = 1ull << 21;  // particles per call
 constexpr uint64_t kNoallocMaxTiles = 1ull << 18;      // 8^3-cell tiles (a 512^3 grid)
 
 constexpr size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
-// Layout: range flag | tile counts | tile starts | per-block tile tables |
+// Layout: range flag | tile counts | tile starts and their block sums |
 // tile-ordered particles.
 constexpr size_t kOffFlag = 0;
 constexpr size_t kOffCount = 256;
 constexpr size_t kOffStart = kOffCount + align256((kNoallocMaxTiles + 1) * sizeof(uint32_t));
-constexpr size_t kOffDump = kOffStart + align256((kNoallocMaxTiles + 1) * sizeof(uint32_t));
-constexpr size_t kOffSorted = kOffDump + align256(kNoallocMaxParticles * sizeof(uint2));
+constexpr size_t kOffSorted = kOffStart + align256((kNoallocMaxTiles + 1 + kNoallocMaxTiles / 1024) * sizeof(uint32_t));
 constexpr size_t kScratchBytes = kOffSorted + align256(kNoallocMaxParticles * sizeof(float4));
 
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
@@ -92,7 +91,7 @@ int pcmcc_deposit_noalloc(pcmcc_ctx* c, const float* x, const float* y, const fl
   if (d.n_tiles > kNoallocMaxTiles)
     return fail(c, PCMCC_EINVAL, "%llu tiles of 8^3 cells exceed the allocation-free deposit's maximum of %llu",
                 (unsigned long long)d.n_tiles, (unsigned long long)kNoallocMaxTiles);
-  if (d.dump_entries > kNoallocMaxParticles || d.sorted > kNoallocMaxParticles)
+  if (d.scan_sums > kNoallocMaxTiles / 1024 || d.sorted > kNoallocMaxParticles)
     return fail(c, PCMCC_EINVAL, "deposit work exceeds the allocation-free scratch");
   HIP_TRY(c, launch_fill_u32(flag, 1, 0u, c->stream));
   if (!d.binned) {
@@ -101,7 +100,6 @@ int pcmcc_deposit_noalloc(pcmcc_ctx* c, const float* x, const float* y, const fl
     DepositWork W;
     W.tile_count = reinterpret_cast<uint32_t*>(base + kOffCount);
     W.tile_start = reinterpret_cast<uint32_t*>(base + kOffStart);
-    W.dump = reinterpret_cast<uint2*>(base + kOffDump);
     W.sorted = reinterpret_cast<float4*>(base + kOffSorted);
     HIP_TRY(c, launch_deposit_binned(x, y, z, w, (uint64_t)n, g, rho, W, c->stream));
   }

@@ -335,18 +335,18 @@ static int ensure_dep_work(pcmcc_ctx* c, const DepositNeeds& d, bool sorted) {
     have = need;
     return PCMCC_OK;
   };
-  // tile_count and tile_start share one capacity (n_tiles + 1 entries each)
+  // tile_count and tile_start share one capacity
+  const uint64_t entries = d.n_tiles + 1 + d.scan_sums;
   int rc = PCMCC_OK;
-  if (c->dep_tiles < d.n_tiles + 1) {
+  if (c->dep_tiles < entries) {
     uint64_t have = 0;
-    rc = grow(&c->dep.tile_count, have, d.n_tiles + 1);
+    rc = grow(&c->dep.tile_count, have, entries);
     have = 0;
-    if (!rc) rc = grow(&c->dep.tile_start, have, d.n_tiles + 1);
-    c->dep_tiles = rc ? 0 : d.n_tiles + 1;
+    if (!rc) rc = grow(&c->dep.tile_start, have, entries);
+    c->dep_tiles = rc ? 0 : entries;
     if (rc) return rc;
   }
-  rc = grow(&c->dep.dump, c->dep_dump, d.dump_entries);
-  if (!rc && sorted) rc = grow(&c->dep.sorted, c->dep_sorted, d.sorted);
+  if (sorted) rc = grow(&c->dep.sorted, c->dep_sorted, d.sorted);
   return rc;
 }
 

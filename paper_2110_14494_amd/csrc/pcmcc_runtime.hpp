@@ -53,7 +53,7 @@ struct pcmcc_ctx {
   float4* fpack = nullptr;  // corner-packed field records
   size_t fpack_recs = 0;
   DepositWork dep{};        // binned deposit buffers
-  uint64_t dep_tiles = 0, dep_dump = 0, dep_sorted = 0;
+  uint64_t dep_tiles = 0, dep_sorted = 0;
   unsigned* emax_bits = nullptr;
   int64_t* host_n = nullptr;  // pinned
   unsigned* dep_err = nullptr;    // deposit range flag (device)
