@@ -42,7 +42,16 @@ constexpr int kBinRange = kBinThreads * kBinPer;        // particles per block
 constexpr int kSortPer = 16;                            // particles per thread of the particle sort
 constexpr int kSortRange = kBinThreads * kSortPer;
 constexpr int kScanTile = 4096;                         // tile counts per block of the prefix sum
-constexpr int kAccRange = 32768;                        // sorted particles per block, accumulation
+// Sorted particles per block of the accumulation: an even share over 2^14
+// blocks, between the limits (a block's flush costs up to 729 global atomics,
+// and few blocks leave the chip idle: with 2^15 particles a block, 9e5
+// particles took 485 us in 29 blocks, 142 us so; 2^24 470 and 341, 1e8 1600 and
+// 917 us).
+constexpr uint32_t kAccMin = 1024, kAccMax = 32768;
+static uint32_t acc_range(uint64_t n) {
+  const uint64_t r = (n / 16384 + 255) / 256 * 256;
+  return (uint32_t)(r < kAccMin ? kAccMin : (r < kAccMax ? r : kAccMax));
+}
 constexpr uint32_t kEmpty = 0xFFFFFFFFu;
 
 // Lower and upper centre index of one axis, clamped to the grid, and the
@@ -436,16 +445,17 @@ __device__ __forceinline__ double accum_run(const float4* __restrict__ sorted, u
 constexpr double kAccGuard = 1073741824.0;
 
 // Pass 3: per-tile sums.  Block b covers sorted particles
-// [b kAccRange, (b+1) kAccRange), one tile at a time.
-__global__ __launch_bounds__(256) void k_dep_accum(const float4* __restrict__ sorted, uint64_t n, TileGeom T,
-                                                    const uint32_t* __restrict__ start, unsigned long long* rho) {
+// [b range, (b + 1) range), one tile at a time.
+__global__ __launch_bounds__(256) void k_dep_accum(const float4* __restrict__ sorted, uint64_t n, uint32_t range,
+                                                    TileGeom T, const uint32_t* __restrict__ start,
+                                                    unsigned long long* rho) {
   __shared__ unsigned long long acc[kTileCells];
   __shared__ uint32_t s_tile;
   __shared__ uint64_t s_end;
   __shared__ double s_wsum;
   for (int c = threadIdx.x; c < kTileCells; c += blockDim.x) acc[c] = 0;
-  uint64_t cur = (uint64_t)blockIdx.x * kAccRange;
-  const uint64_t end = cur + kAccRange < n ? cur + kAccRange : n;
+  uint64_t cur = (uint64_t)blockIdx.x * range;
+  const uint64_t end = cur + range < n ? cur + range : n;
   while (cur < end) {
     if (threadIdx.x == 0) {
       const float4 q = sorted[cur];
@@ -558,8 +568,8 @@ hipError_t launch_deposit_binned(const float* x, const float* y, const float* z,
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_dep_scatter, dim3((unsigned)((n + kBinRange - 1) / kBinRange)), dim3(kBinThreads), 0, stream, x,
                      y, z, w, n, T, W.tile_count, W.sorted);
-  const uint64_t na = (n + kAccRange - 1) / kAccRange;
-  hipLaunchKernelGGL(k_dep_accum, dim3((unsigned)na), dim3(256), 0, stream, W.sorted, n, T, W.tile_start,
+  const uint32_t range = acc_range(n);
+  hipLaunchKernelGGL(k_dep_accum, dim3((unsigned)((n + range - 1) / range)), dim3(256), 0, stream, W.sorted, n, range, T, W.tile_start,
                      (unsigned long long*)rho);
   return hipGetLastError();
 }
