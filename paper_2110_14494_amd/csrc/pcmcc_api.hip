@@ -96,6 +96,8 @@ int pcmcc_destroy(pcmcc_ctx* c) {
   dfree(c->fl_tab);
   if (c->sc_host) (void)hipHostFree(c->sc_host);
   dfree(c->emax_bits);
+  dfree(c->reach_rows);
+  dfree(c->reach);
   dfree(c->dep_err);
   if (c->host_ctl) (void)hipHostFree(c->host_ctl);
   if (c->host_n) (void)hipHostFree(c->host_n);

@@ -290,10 +290,34 @@ hipError_t launch_fill_u32(uint32_t* p, uint64_t n, uint32_t v, hipStream_t stre
 // the grid); needs W's tile counts and starts as the binned deposit.
 hipError_t launch_sort_tiles(const Soa& src, uint64_t n, const DepositGeom& g, const DepositWork& W, const Soa& dst,
                              hipStream_t stream);
-hipError_t launch_field_bounds(const float4* E, int nx, int ny, int nz, float2* out, unsigned* emax_bits,
-                               hipStream_t stream);
-hipError_t launch_pack_field(const float4* E, const float2* bound, int nx, int ny, int nz, float4* P,
-                             hipStream_t stream);
+// A box of indices, [lo, hi) per axis.
+struct CellBox {
+  int lo[3], hi[3];
+};
+// The records (lower indices within [-1, n] per axis) that a call's particles
+// can gather from, and the cells whose bounds these hold.
+struct FieldBox {
+  CellBox rec, cells;
+  int whole;
+};
+struct ReachArgs {
+  Soa p;
+  uint64_t n;
+  const float4* E;
+  int dim[3];
+  double x0[3], dx;
+  double t, qm, rounding;  // time of the call, |charge / mass|, rounding of a position over the call's steps
+};
+constexpr int kReachBlocks = 2048;
+constexpr size_t kReachFloats = 9 * (size_t)kReachBlocks;  // launch_reach's rows
+// The box, and the largest |E| (0 where the box is the whole grid).
+hipError_t launch_reach(const ReachArgs& A, float* rows, FieldBox* box, unsigned* emax_bits, hipStream_t stream);
+// Field bounds of the cells of `reach` (null: of the grid); the largest |E|
+// of the grid to emax_bits unless launch_reach has set it.
+hipError_t launch_field_bounds(const float4* E, int nx, int ny, int nz, const FieldBox* reach, float2* out,
+                               unsigned* emax_bits, hipStream_t stream);
+hipError_t launch_pack_field(const float4* E, const float2* bound, int nx, int ny, int nz, const FieldBox* reach,
+                             float4* P, hipStream_t stream);
 hipError_t launch_build_tables(const TableBuild& B, float* C, float* P, float* nu, hipStream_t stream);
 hipError_t launch_philox(const uint32_t* ctr, Key key, uint32_t* out, int64_t n, hipStream_t stream);
 hipError_t launch_lookup(const TableView& T, const SpeciesView& S, const float* eps, float* cum, const float* s_ub,

@@ -552,13 +552,20 @@ __device__ __forceinline__ void box_add(Box7& b, const Box7& o) {
 }
 
 __global__ __launch_bounds__(kFbThreads) void k_field_bounds(const float4* __restrict__ E, int nx, int ny, int nz,
-                                                             float2* __restrict__ out, unsigned* __restrict__ emax_bits) {
+                                                             const FieldBox* __restrict__ reach,
+                                                             float2* __restrict__ out,
+                                                             unsigned* __restrict__ emax_bits) {
   __shared__ float4 s_e[kFbIn];  // (Ex, Ey, Ez, |E|), |E| < 0 outside the grid
   __shared__ float s_x[7][kFbXR];
   __shared__ float s_w[kFbThreads / 64];
-  const int gx0 = (int)blockIdx.x * kFbTX - 1, gy0 = (int)blockIdx.y * kFbTY - 1;
-  const int per = (nz + (int)gridDim.z - 1) / (int)gridDim.z;
-  const int k0 = (int)blockIdx.z * per, k1 = min(nz, k0 + per);
+  const CellBox box = reach ? reach->cells : CellBox{{0, 0, 0}, {nx, ny, nz}};
+  // tiles of x and y by ranges of at least 16 planes, as many as there are blocks for
+  const int tiles_x = (box.hi[0] - box.lo[0] + kFbTX - 1) / kFbTX, tiles_y = (box.hi[1] - box.lo[1] + kFbTY - 1) / kFbTY;
+  const int tiles = tiles_x * tiles_y, depth = box.hi[2] - box.lo[2];
+  const int chunks = max(1, min((int)gridDim.x / tiles, depth / 16)), per = (depth + chunks - 1) / chunks;
+  const int tile = (int)blockIdx.x % tiles, chunk = (int)blockIdx.x / tiles;
+  const int gx0 = box.lo[0] + tile % tiles_x * kFbTX - 1, gy0 = box.lo[1] + tile / tiles_x * kFbTY - 1;
+  const int k0 = box.lo[2] + chunk * per, k1 = min(box.hi[2], k0 + per);
   const int tid = threadIdx.x, tx = tid % kFbTX, ty = tid / kFbTX;
   float local_max = 0.0f;
   if (k0 < k1) {  // block-uniform
@@ -612,7 +619,7 @@ __global__ __launch_bounds__(kFbThreads) void k_field_bounds(const float4* __res
       r2 = r3;
       r3 = nv;
       const int k = kk - 2, i = gx0 + 1 + tx, j = gy0 + 1 + ty;
-      if (k >= k0 && i < nx && j < ny) {
+      if (k >= k0 && i < box.hi[0] && j < box.hi[1]) {
         Box7 b = r0;
         box_add(b, r1);
         box_add(b, r2);
@@ -629,8 +636,134 @@ __global__ __launch_bounds__(kFbThreads) void k_field_bounds(const float4* __res
   if (tid == 0) {
     float m = 0.0f;
     for (int w = 0; w < kFbThreads / 64; ++w) m = fmaxf(m, s_w[w]);
-    if (m > 0.0f) atomicMax(emax_bits, __float_as_uint(m));
+    if (m > 0.0f && (!reach || reach->whole)) atomicMax(emax_bits, __float_as_uint(m));
   }
+}
+
+// What the particles of a call can reach, in two kernels.  k_reach writes per
+// block the least and largest x, y, z, the largest |v|^2, 1 if any of them or
+// of the fields is not finite, and the largest |E| (rounded as in
+// k_field_bounds); it reads the field and the particles once, at the rate of a
+// copy (0.80 ms for 512^3 cells and 2^26 particles).  Where 64 of
+// the particles already span most of the grid the blocks return with the flag
+// set: a few microseconds (55 us with 1024 of them, read by every block).
+//
+// k_reach_box makes the box: the particles', wider by the way the fastest can
+// go under the largest acceleration, and one cell.  Collisions never raise a
+// speed, newborns start where their parents are and no faster, and the
+// interpolated field is at most the largest.
+constexpr float kReachMost = 0.75f;  // of the grid: the whole is formed then
+constexpr int kReachRow = 9;
+__device__ __forceinline__ bool reach_least(int q) { return q < 6 && (q & 1) == 0; }
+__device__ __forceinline__ void reach_reduce(float (&r)[kReachRow], float (*s_w)[kReachRow]) {  // to every thread
+#pragma unroll
+  for (int q = 0; q < kReachRow; ++q) {
+    for (int off = 32; off > 0; off >>= 1) {
+      const float o = __shfl_xor(r[q], off);
+      r[q] = reach_least(q) ? fminf(r[q], o) : fmaxf(r[q], o);
+    }
+    if ((threadIdx.x & 63) == 0) s_w[threadIdx.x / 64][q] = r[q];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < kReachRow; ++q)
+    for (int w = 0; w < 4; ++w) r[q] = reach_least(q) ? fminf(r[q], s_w[w][q]) : fmaxf(r[q], s_w[w][q]);
+  __syncthreads();
+}
+__device__ __forceinline__ void reach_add(float (&r)[kReachRow], const Soa& p, uint64_t i) {
+  const float x = p.x[i], y = p.y[i], z = p.z[i], vx = p.vx[i], vy = p.vy[i], vz = p.vz[i];
+  const float v2 = fmaf(vz, vz, fmaf(vy, vy, vx * vx));
+  r[0] = fminf(r[0], x);
+  r[1] = fmaxf(r[1], x);
+  r[2] = fminf(r[2], y);
+  r[3] = fmaxf(r[3], y);
+  r[4] = fminf(r[4], z);
+  r[5] = fmaxf(r[5], z);
+  r[6] = fmaxf(r[6], v2);
+  if (!(fabsf(x) < INFINITY && fabsf(y) < INFINITY && fabsf(z) < INFINITY && v2 < INFINITY)) r[7] = 1.0f;
+}
+
+__global__ __launch_bounds__(256) void k_reach(ReachArgs A, float* __restrict__ out) {
+  __shared__ float s_w[4][kReachRow];
+  const float none[kReachRow] = {INFINITY, -INFINITY, INFINITY, -INFINITY, INFINITY, -INFINITY, 0.0f, 0.0f, 0.0f};
+  float r[kReachRow];
+#pragma unroll
+  for (int q = 0; q < kReachRow; ++q) r[q] = none[q];
+  if (threadIdx.x < 64) {
+    const uint64_t i = (uint64_t)threadIdx.x * ((A.n + 63) / 64);
+    if (i < A.n) reach_add(r, A.p, i);
+  }
+  reach_reduce(r, s_w);
+  float part = 1.0f;
+#pragma unroll
+  for (int q = 0; q < 3; ++q) part *= fminf(1.0f, (r[2 * q + 1] - r[2 * q]) / ((float)A.dim[q] * (float)A.dx));
+  if (part > kReachMost || r[7] != 0.0f) {
+    if (threadIdx.x == 0) out[kReachRow * blockIdx.x + 7] = 1.0f;
+    return;
+  }
+#pragma unroll
+  for (int q = 0; q < kReachRow; ++q) r[q] = none[q];
+  const uint64_t stride = (uint64_t)gridDim.x * 256, t0 = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+  const uint64_t cells = (uint64_t)A.dim[0] * (uint64_t)A.dim[1] * (uint64_t)A.dim[2];
+  for (uint64_t c = t0; c < cells; c += 4 * stride) {
+    float4 v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      v[q] = c + q * stride < cells ? A.E[c + q * stride] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float e = sqrtf(fmaf(v[q].z, v[q].z, fmaf(v[q].x, v[q].x, v[q].y * v[q].y)));
+      r[8] = fmaxf(r[8], e);
+      if (!(e < INFINITY)) r[7] = 1.0f;
+    }
+  }
+#pragma unroll 4
+  for (uint64_t i = t0; i < A.n; i += stride) reach_add(r, A.p, i);
+  reach_reduce(r, s_w);
+  if (threadIdx.x == 0)
+    for (int q = 0; q < kReachRow; ++q) out[kReachRow * blockIdx.x + q] = r[q];
+}
+
+__global__ __launch_bounds__(256) void k_reach_box(ReachArgs A, const float* __restrict__ rows,
+                                                   FieldBox* __restrict__ out, unsigned* __restrict__ emax_bits) {
+  __shared__ float s_w[4][kReachRow];
+  float r[kReachRow] = {INFINITY, -INFINITY, INFINITY, -INFINITY, INFINITY, -INFINITY, 0.0f, 0.0f, 0.0f};
+  for (int b = threadIdx.x; b < kReachBlocks; b += 256) {
+#pragma unroll
+    for (int q = 0; q < kReachRow; ++q) {
+      const float o = rows[kReachRow * b + q];
+      r[q] = reach_least(q) ? fminf(r[q], o) : fmaxf(r[q], o);
+    }
+  }
+  reach_reduce(r, s_w);
+  if (threadIdx.x != 0) return;
+  FieldBox f;
+  bool whole = r[7] != 0.0f;
+  // 1 % and one cell beyond the rounding of the positions stored at each step
+  const double way = 1.01 * (sqrt((double)r[6]) * A.t + 0.5 * A.qm * (double)r[8] * A.t * A.t);
+  double part = 1.0;
+  for (int q = 0; q < 3; ++q) {
+    const double lo = (double)r[2 * q], hi = (double)r[2 * q + 1];
+    const double more = way + A.rounding * fmax(fabs(lo), fabs(hi));
+    const double ul = floor((lo - more - A.x0[q]) / A.dx - 0.5) - 1.0;
+    const double uh = floor((hi + more - A.x0[q]) / A.dx - 0.5) + 1.0;
+    if (!(fabs(ul) < INFINITY && fabs(uh) < INFINITY)) whole = true;
+    f.rec.lo[q] = (int)fmin(fmax(ul, -1.0), (double)A.dim[q]);
+    f.rec.hi[q] = (int)fmin(fmax(uh, -1.0), (double)A.dim[q]) + 1;
+    part *= (double)(f.rec.hi[q] - f.rec.lo[q]) / (A.dim[q] + 2);
+  }
+  whole = whole || !(part <= (double)kReachMost);
+  for (int q = 0; q < 3; ++q) {
+    if (whole) {
+      f.rec.lo[q] = -1;
+      f.rec.hi[q] = A.dim[q] + 1;
+    }
+    f.cells.lo[q] = min(max(f.rec.lo[q], 0), A.dim[q] - 1);
+    f.cells.hi[q] = min(max(f.rec.hi[q] - 1, 0), A.dim[q] - 1) + 1;
+  }
+  f.whole = whole;
+  *out = f;
+  *emax_bits = whole ? 0u : __float_as_uint(r[8]);  // of the whole: by k_field_bounds
 }
 
 // Corner-packed field (layout in pcmcc_device.hpp): one thread per record,
@@ -640,51 +773,61 @@ __global__ __launch_bounds__(kFbThreads) void k_field_bounds(const float4* __res
 // record order, forms them in registers, stages them in LDS and writes them
 // out as consecutive float4s: each store instruction then covers 1 KiB of
 // consecutive records instead of one 16-byte piece of 64 different records.
+// With `reach` only the records that the call's particles can gather from are
+// formed.
 constexpr int kPackThreads = 128;
 constexpr int kPackStride = kRecFloats / 4 + 1;  // float4 per record in LDS (one of padding spreads the banks)
 __global__ __launch_bounds__(kPackThreads) void k_pack_field(const float4* __restrict__ E,
                                                              const float2* __restrict__ bound, int nx, int ny,
-                                                             int nz, float4* __restrict__ P) {
+                                                             int nz, const FieldBox* __restrict__ reach,
+                                                             float4* __restrict__ P) {
   __shared__ float4 st[kPackThreads * kPackStride];
-  const uint32_t px = (uint32_t)nx + 2, py = (uint32_t)ny + 2;
-  const uint32_t nrec = px * py * ((uint32_t)nz + 2);  // below 2^31 (checked by the caller)
-  const uint32_t r0 = blockIdx.x * kPackThreads;
-  const uint32_t r = r0 + threadIdx.x;
-  if (r < nrec) {
-    const uint32_t row = r / px, ri = r - row * px;
-    const uint32_t rk = row / py, rj = row - rk * py;
-    const int i = (int)ri - 1, j = (int)rj - 1, k = (int)rk - 1;
-    const int ci[2] = {min(max(i, 0), nx - 1), min(max(i + 1, 0), nx - 1)};
-    const int cj[2] = {min(max(j, 0), ny - 1), min(max(j + 1, 0), ny - 1)};
-    const int ck[2] = {min(max(k, 0), nz - 1), min(max(k + 1, 0), nz - 1)};
-    float v[kRecFloats];
+  __shared__ uint32_t at[kPackThreads];  // the records' places
+  const CellBox box = reach ? reach->rec : CellBox{{-1, -1, -1}, {nx + 1, ny + 1, nz + 1}};
+  const uint32_t bx = (uint32_t)(box.hi[0] - box.lo[0]), by = (uint32_t)(box.hi[1] - box.lo[1]);
+  const uint32_t nrec = bx * by * (uint32_t)(box.hi[2] - box.lo[2]);  // below 2^31 (checked by the caller)
+  for (uint32_t r0 = blockIdx.x * kPackThreads; r0 < nrec; r0 += gridDim.x * kPackThreads) {
+    const uint32_t r = r0 + threadIdx.x;
+    if (r < nrec) {
+      const uint32_t row = r / bx, ri = r - row * bx;
+      const uint32_t rk = row / by, rj = row - rk * by;
+      const int i = (int)ri + box.lo[0], j = (int)rj + box.lo[1], k = (int)rk + box.lo[2];
+      at[threadIdx.x] =
+          ((uint32_t)(k + 1) * ((uint32_t)ny + 2) + (uint32_t)(j + 1)) * ((uint32_t)nx + 2) + (uint32_t)(i + 1);
+      const int ci[2] = {min(max(i, 0), nx - 1), min(max(i + 1, 0), nx - 1)};
+      const int cj[2] = {min(max(j, 0), ny - 1), min(max(j + 1, 0), ny - 1)};
+      const int ck[2] = {min(max(k, 0), nz - 1), min(max(k + 1, 0), nz - 1)};
+      float v[kRecFloats];
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      const float4 e = E[((size_t)ck[c >> 2] * ny + cj[(c >> 1) & 1]) * nx + ci[c & 1]];
-      v[3 * c] = e.x;
-      v[3 * c + 1] = e.y;
-      v[3 * c + 2] = e.z;
+      for (int c = 0; c < 8; ++c) {
+        const float4 e = E[((size_t)ck[c >> 2] * ny + cj[(c >> 1) & 1]) * nx + ci[c & 1]];
+        v[3 * c] = e.x;
+        v[3 * c + 1] = e.y;
+        v[3 * c + 2] = e.z;
+      }
+      // the dx = 1 corners as differences along x (rounded as the gather
+      // would round them)
+#pragma unroll
+      for (int c = 1; c < 8; c += 2)
+#pragma unroll
+        for (int q = 0; q < 3; ++q) v[3 * c + q] = v[3 * c + q] - v[3 * (c - 1) + q];
+      const float2 b = bound[((size_t)ck[0] * ny + cj[0]) * nx + ci[0]];
+      v[24] = b.x;
+      v[25] = b.y;
+#pragma unroll
+      for (int q = 26; q < kRecFloats; ++q) v[q] = 0.0f;
+#pragma unroll
+      for (int q = 0; q < kRecFloats / 4; ++q)
+        st[threadIdx.x * kPackStride + q] = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
     }
-    // the dx = 1 corners as differences along x (rounded as the gather
-    // would round them)
-#pragma unroll
-    for (int c = 1; c < 8; c += 2)
-#pragma unroll
-      for (int q = 0; q < 3; ++q) v[3 * c + q] = v[3 * c + q] - v[3 * (c - 1) + q];
-    const float2 b = bound[((size_t)ck[0] * ny + cj[0]) * nx + ci[0]];
-    v[24] = b.x;
-    v[25] = b.y;
-#pragma unroll
-    for (int q = 26; q < kRecFloats; ++q) v[q] = 0.0f;
-#pragma unroll
-    for (int q = 0; q < kRecFloats / 4; ++q)
-      st[threadIdx.x * kPackStride + q] = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+    __syncthreads();
+    const uint32_t nb = min((uint32_t)kPackThreads, nrec - r0);  // records of this block
+    for (uint32_t f = threadIdx.x; f < nb * (kRecFloats / 4); f += kPackThreads) {
+      const uint32_t q = f / (kRecFloats / 4), w = f % (kRecFloats / 4);
+      P[(size_t)at[q] * (kRecFloats / 4) + w] = st[q * kPackStride + w];
+    }
+    __syncthreads();  // the next records overwrite st
   }
-  __syncthreads();
-  const uint32_t nb = min((uint32_t)kPackThreads, nrec - r0);  // records of this block
-  float4* out = P + (size_t)r0 * (kRecFloats / 4);
-  for (uint32_t f = threadIdx.x; f < nb * (kRecFloats / 4); f += kPackThreads)
-    out[f] = st[(f / (kRecFloats / 4)) * kPackStride + f % (kRecFloats / 4)];
 }
 
 // ---------------------------------------------------------------------------
@@ -802,23 +945,30 @@ hipError_t launch_finalize(const Soa& user, const Soa& scratch, Ctl* ctl, int64_
   return hipGetLastError();
 }
 
-hipError_t launch_field_bounds(const float4* E, int nx, int ny, int nz, float2* out, unsigned* emax_bits,
-                               hipStream_t stream) {
-  const unsigned tx = (unsigned)((nx + kFbTX - 1) / kFbTX), ty = (unsigned)((ny + kFbTY - 1) / kFbTY);
-  unsigned chunks = (2048 + tx * ty - 1) / (tx * ty);  // plane ranges: about 2048 blocks, at least 16 planes each
+hipError_t launch_reach(const ReachArgs& A, float* rows, FieldBox* box, unsigned* emax_bits, hipStream_t stream) {
+  hipLaunchKernelGGL(k_reach, dim3(kReachBlocks), dim3(256), 0, stream, A, rows);
+  hipLaunchKernelGGL(k_reach_box, dim3(1), dim3(256), 0, stream, A, rows, box, emax_bits);
+  return hipGetLastError();
+}
+
+hipError_t launch_field_bounds(const float4* E, int nx, int ny, int nz, const FieldBox* reach, float2* out,
+                               unsigned* emax_bits, hipStream_t stream) {
+  const unsigned tiles = (unsigned)((nx + kFbTX - 1) / kFbTX) * (unsigned)((ny + kFbTY - 1) / kFbTY);
+  unsigned chunks = (2048 + tiles - 1) / tiles;  // plane ranges: about 2048 blocks, at least 16 planes each
   if (chunks > (unsigned)(nz / 16)) chunks = (unsigned)(nz / 16);
   if (chunks < 1) chunks = 1;
-  hipLaunchKernelGGL(k_field_bounds, dim3(tx, ty, chunks), dim3(kFbThreads), 0, stream, E, nx, ny, nz, out,
+  hipLaunchKernelGGL(k_field_bounds, dim3(tiles * chunks), dim3(kFbThreads), 0, stream, E, nx, ny, nz, reach, out,
                      emax_bits);
   return hipGetLastError();
 }
 
-hipError_t launch_pack_field(const float4* E, const float2* bound, int nx, int ny, int nz, float4* P,
-                             hipStream_t stream) {
-  const uint64_t nrec = ((uint64_t)nx + 2) * ((uint64_t)ny + 2) * ((uint64_t)nz + 2);
+hipError_t launch_pack_field(const float4* E, const float2* bound, int nx, int ny, int nz, const FieldBox* reach,
+                             float4* P, hipStream_t stream) {
+  const uint64_t nrec = (uint64_t)(nx + 2) * (uint64_t)(ny + 2) * (uint64_t)(nz + 2);
   if (nrec >= ((uint64_t)1 << 31)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_pack_field, dim3((unsigned)((nrec + kPackThreads - 1) / kPackThreads)), dim3(kPackThreads), 0,
-                     stream, E, bound, nx, ny, nz, P);
+  const uint64_t b = (nrec + kPackThreads - 1) / kPackThreads;
+  hipLaunchKernelGGL(k_pack_field, dim3((unsigned)std::min<uint64_t>(b, 1 << 17)), dim3(kPackThreads), 0, stream, E,
+                     bound, nx, ny, nz, reach, P);
   return hipGetLastError();
 }
 

@@ -55,6 +55,8 @@ struct pcmcc_ctx {
   DepositWork dep{};        // binned deposit buffers
   uint64_t dep_tiles = 0, dep_sorted = 0;
   unsigned* emax_bits = nullptr;
+  float* reach_rows = nullptr;  // launch_reach
+  FieldBox* reach = nullptr;
   int64_t* host_n = nullptr;  // pinned
   unsigned* dep_err = nullptr;    // deposit range flag (device)
   unsigned* host_err = nullptr;   // pinned copy of it
@@ -179,7 +181,7 @@ bool valid_grid(const pcmcc_grid* g);
 TableView table_view(const pcmcc_ctx* c);
 SpeciesView species_view(const pcmcc_ctx* c);
 int check_ready(pcmcc_ctx* c);
-int prepare_field(pcmcc_ctx* c, const pcmcc_grid* g);
+int prepare_field(pcmcc_ctx* c, const pcmcc_grid* g, const Soa& parts, uint64_t n, double dt, int n_steps);
 int deposit_range_check(pcmcc_ctx* c);
 int run_deposit(pcmcc_ctx* c, const float* x, const float* y, const float* z, const float* w, const int64_t* n_dev,
                 uint64_t n, const pcmcc_grid* grid, int64_t* rho, bool check = true);
