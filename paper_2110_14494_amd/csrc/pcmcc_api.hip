@@ -95,6 +95,8 @@ int pcmcc_destroy(pcmcc_ctx* c) {
   dfree(c->fl_store);
   dfree(c->fl_tab);
   if (c->sc_host) (void)hipHostFree(c->sc_host);
+  dfree(c->infer_dev);
+  if (c->infer_host) (void)hipHostFree(c->infer_host);
   dfree(c->emax_bits);
   dfree(c->reach_rows);
   dfree(c->reach);

@@ -93,6 +93,9 @@ struct pcmcc_ctx {
   uint64_t ev_cap = 0;
   unsigned long long* sc_red = nullptr;  // [0] max |f| bits [1] max |r| bits [2] ne max [3] first cell [4] sum w [5..6] events [7] photons
   unsigned long long* sc_host = nullptr;  // pinned copy
+  // surrogate inference (infer_space)
+  uint8_t *infer_dev = nullptr, *infer_host = nullptr;  // the latter pinned
+  size_t infer_bytes = 0;
   SelState* sel = nullptr;
   unsigned* sel_hist = nullptr;
   // fluid step: predicted densities and first-stage derivatives (6 grids), table
