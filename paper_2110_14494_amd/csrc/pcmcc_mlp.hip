@@ -511,20 +511,32 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
     }
     L.A3[s][l] = v;
   }
+  // The row sums of the bfloat16 weights, exact in double in any order: four
+  // threads a row of W2, 32 a row of W3 (one thread a row took 64 loads of 64
+  // rows each one after another: WAS -> NOW us a launch at 1000 points).
+  {
+    const int row = tid >> 2, part = tid & 3;
+    double rs = 0.0;
+#pragma unroll
+    for (int k = part; k < kH; k += 4) rs += (double)(float)(__bf16)P[OFF_W2 + row * kH + k];
+    rs += __shfl_xor(rs, 1);
+    rs += __shfl_xor(rs, 2);
+    if (part == 0) L.c2[row] = kM2L2E * (float)((double)P[OFF_B2 + row] - rs);
+  }
   if (tid < 64) {
     L.a1[tid] = kM2L2E * P[OFF_W1 + tid];
     L.c1[tid] = kM2L2E * P[OFF_B1 + tid];
-    // the row sum of the bfloat16 weights in a fixed order (exact in double)
-    double rs = 0.0;
-    for (int k = 0; k < kH; ++k) rs += (double)(float)(__bf16)P[OFF_W2 + tid * kH + k];
-    L.c2[tid] = kM2L2E * (float)((double)P[OFF_B2 + tid] - rs);
   }
-  if (tid < 8) {
+  {
+    const int row = tid >> 5, part = tid & 31;  // 8 rows, of which kOut there are
     double rs = 0.0;
-    if (tid < kOut)
-      for (int j = 0; j < kH; ++j) rs += (double)(float)(__bf16)P[OFF_W3 + tid * kH + j];
-    L.y_scale[tid] = tid < kOut ? 2.0f * A.sd_y[tid] : 0.0f;
-    L.y_off[tid] = tid < kOut ? (float)(((double)P[OFF_B3 + tid] - rs) * A.sd_y[tid] + A.mu_y[tid]) : 0.0f;
+    if (row < kOut)
+      for (int j = part; j < kH; j += 32) rs += (double)(float)(__bf16)P[OFF_W3 + row * kH + j];
+    for (int d = 1; d < 32; d <<= 1) rs += __shfl_xor(rs, d);
+    if (part == 0) {
+      L.y_scale[row] = row < kOut ? 2.0f * A.sd_y[row] : 0.0f;
+      L.y_off[row] = row < kOut ? (float)(((double)P[OFF_B3 + row] - rs) * A.sd_y[row] + A.mu_y[row]) : 0.0f;
+    }
   }
   const bool mask_lds = A.n_cells <= kMaskLds;
   if (mask_lds)
