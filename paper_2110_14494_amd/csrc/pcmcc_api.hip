@@ -68,12 +68,11 @@ int pcmcc_destroy(pcmcc_ctx* c) {
   dfree(c->dep.tile_start);
   dfree(c->dep.sorted);
   dfree(c->wt.cls);
+  dfree(c->wt.cand);
   dfree(c->wt.idx0);
-  dfree(c->wt.idx1);
   dfree(c->wt.key0);
   dfree(c->wt.key1);
   dfree(c->wt.key2);
-  dfree(c->wt.pos);
   dfree(c->wt.cnt);
   dfree(c->wt.counters);
   dfree(c->wt.temp);

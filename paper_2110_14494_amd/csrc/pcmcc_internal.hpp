@@ -147,13 +147,20 @@ struct WeightGeom {
   int cell_bits;      // bits of the largest cell index
   uint64_t capacity;  // slots of the output buffer
 };
+struct WeightCand {  // merge candidate
+  uint64_t id;
+  uint32_t index;  // of the particle
+  float w;
+};
 struct WeightWork {
   uint8_t* cls;                 // [n] class per particle
-  uint32_t *idx0, *idx1;        // [n] candidate indices (sort ping-pong)
+  WeightCand* cand;             // [n] candidates by slot
+  uint32_t* idx0;               // [n] sorted slots
   uint64_t *key0, *key1;        // [n] sort keys
   uint64_t* key2;               // [n] candidates' (cell, energy) keys by slot
-  uint32_t *pos, *cnt;          // [n] output counts and positions
-  unsigned long long* counters;  // [4] candidates, merged pairs
+  uint32_t* cnt;                // [n] output counts
+  uint32_t *idx1, *pos;         // [n] run starts and positions, in key0's memory (used after the sorts)
+  unsigned long long* counters;  // [4] candidates, merged pairs, long run of equal keys, candidates at rest
   void* temp;
   size_t temp_bytes;
 };

@@ -12,9 +12,11 @@
 // (second, third) words of the particle's weight-update draw.
 //
 // Schedule: classify (blocks of 2048 particles read in order; candidates
-// appended with one atomic per block, each with its id and its (cell,
-// energy) key), two stable radix sorts of the candidates (by id, then by
-// cell and energy; rocPRIM), run starts of the cells by a max-scan, pairing
+// appended with one atomic per block, each with a record of what the pairing
+// needs and its (cell, energy) key), a radix sort of the candidates by that key
+// (rocPRIM), runs of equal keys put in order of the ids (k_wt_ties; where a
+// run is long two stable sorts instead, by id, then by the key), run starts of
+// the cells by a max-scan, pairing
 // (one thread per candidate position), and an exclusive scan of the output
 // counts (0 removed, 1 kept, 2 split) that places every particle and copy in
 // the other particle buffer.  All the decisions are integer or taken in the
@@ -62,11 +64,10 @@ constexpr int kWtTile = kWtBlock * kWtPer;
 // Classification of tile [base, base + kWtTile): particle base + j kWtBlock
 // + threadIdx.x for j < kWtPer (coalesced).  The merge candidates of a tile
 // take consecutive slots reserved with one atomic; slot k holds the
-// particle's index, id and (cell << 32 | energy bits) key.
+// particle's record and (cell << 32 | energy bits) key.
 __global__ __launch_bounds__(kWtBlock) void k_wt_classify(Soa cur, uint64_t n, WeightGeom g,
                                                            const int64_t* __restrict__ rho, uint8_t* __restrict__ cls,
-                                                           uint32_t* __restrict__ cand_idx,
-                                                           uint64_t* __restrict__ cand_id,
+                                                           WeightCand* __restrict__ cand,
                                                            uint64_t* __restrict__ cand_key,
                                                            unsigned long long* n_cand) {
 #pragma clang fp contract(off)
@@ -114,35 +115,61 @@ __global__ __launch_bounds__(kWtBlock) void k_wt_classify(Soa cur, uint64_t n, W
     if (threadIdx.x == 0) s_base = total ? atomicAdd(n_cand, (unsigned long long)total) : 0ull;
     __syncthreads();
     uint64_t k = s_base + before + (incl - mine);
+    uint32_t rest = 0;
 #pragma unroll
     for (int j = 0; j < kWtPer; ++j) {
       if (merge & (1u << j)) {
         const uint64_t i = base + (uint64_t)j * kWtBlock + threadIdx.x;
-        cand_idx[k] = (uint32_t)i;
-        cand_id[k] = cur.id[i];
-        cand_key[k] = (cell[j] << 32) | wt_energy_bits(cur.vx[i], cur.vy[i], cur.vz[i]);
+        const uint32_t energy = wt_energy_bits(cur.vx[i], cur.vy[i], cur.vz[i]);
+        rest += energy == 0;
+        cand[k] = WeightCand{cur.id[i], (uint32_t)i, cur.w[i]};
+        cand_key[k] = (cell[j] << 32) | energy;
         ++k;
       }
+    }
+    if (__any(rest != 0)) {
+      for (int d = 32; d > 0; d >>= 1) rest += __shfl_xor(rest, d);
+      if (lane_id() == 0) atomicAdd(n_cand + 3, (unsigned long long)rest);
     }
     __syncthreads();  // s_wave and s_base are reused by the next tile
   }
 }
 
-// After the sort by id (values: candidate slots), the slots' particle
-// indices and (cell, energy) keys in that order.
-__global__ void k_wt_key2(const uint32_t* __restrict__ slot, uint64_t m, const uint32_t* __restrict__ cand_idx,
-                          const uint64_t* __restrict__ cand_key, uint32_t* __restrict__ idx,
-                          uint64_t* __restrict__ key2) {
-  for (uint64_t k = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; k < m; k += (uint64_t)gridDim.x * blockDim.x) {
-    const uint32_t sk = slot[k];
-    idx[k] = cand_idx[sk];
-    key2[k] = cand_key[sk];
+// Runs of up to kWtTies equal keys in order of the ids, by the thread of the
+// run's first position; *longer is set for a longer one.
+constexpr uint64_t kWtTies = 32;
+__global__ void k_wt_ties(const uint64_t* __restrict__ key, uint64_t m, const WeightCand* __restrict__ cand,
+                          uint32_t* __restrict__ slot, unsigned long long* longer) {
+  for (uint64_t k = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; k + 1 < m; k += (uint64_t)gridDim.x * blockDim.x) {
+    const uint64_t here = key[k];
+    if (key[k + 1] != here || (k > 0 && key[k - 1] == here)) continue;
+    uint64_t len = 2;
+    while (len <= kWtTies && k + len < m && key[k + len] == here) ++len;
+    if (len > kWtTies) {
+      *longer = 1;
+      continue;
+    }
+    for (uint64_t a = 1; a < len; ++a) {  // insertion
+      const uint32_t s = slot[k + a];
+      const uint64_t id = cand[s].id;
+      uint64_t b = a;
+      for (; b > 0 && cand[slot[k + b - 1]].id > id; --b) slot[k + b] = slot[k + b - 1];
+      slot[k + b] = s;
+    }
   }
 }
 
-__global__ void k_wt_iota(uint32_t* __restrict__ a, uint64_t m) {
+__global__ void k_wt_ids(const WeightCand* __restrict__ cand, uint64_t m, uint64_t* __restrict__ id) {
   for (uint64_t k = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; k < m; k += (uint64_t)gridDim.x * blockDim.x)
-    a[k] = (uint32_t)k;
+    id[k] = cand[k].id;
+}
+
+// After the sort by id (values: candidate slots), the slots' (cell, energy)
+// keys in that order.
+__global__ void k_wt_key2(const uint32_t* __restrict__ slot, uint64_t m, const uint64_t* __restrict__ cand_key,
+                          uint64_t* __restrict__ key2) {
+  for (uint64_t k = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; k < m; k += (uint64_t)gridDim.x * blockDim.x)
+    key2[k] = cand_key[slot[k]];
 }
 
 __global__ void k_wt_heads(const uint64_t* __restrict__ key2, uint64_t m, uint32_t* __restrict__ head) {
@@ -150,17 +177,21 @@ __global__ void k_wt_heads(const uint64_t* __restrict__ key2, uint64_t m, uint32
     head[k] = (k == 0 || (key2[k] >> 32) != (key2[k - 1] >> 32)) ? (uint32_t)k : 0u;
 }
 
-__global__ void k_wt_pair(const uint64_t* __restrict__ key2, const uint32_t* __restrict__ idx,
-                          const uint32_t* __restrict__ run_start, uint64_t m, Soa cur, uint8_t* __restrict__ cls,
+// Bound by access in the candidates' random order: one record of 16 B is read
+// per candidate, a weight and a class written per pair (758 us with the weight
+// and the id read from the particles' arrays, 552 us so, for 2^24 particles).
+__global__ void k_wt_pair(const uint64_t* __restrict__ key2, const uint32_t* __restrict__ slot,
+                          const WeightCand* __restrict__ cand, const uint32_t* __restrict__ run_start, uint64_t m, Soa cur, uint8_t* __restrict__ cls,
                           Key key, uint32_t update_index, unsigned long long* n_pairs) {
   unsigned long long pairs = 0;  // the wave's pairs, counted by lane 0
   for (uint64_t base = (uint64_t)blockIdx.x * blockDim.x; base < m; base += (uint64_t)gridDim.x * blockDim.x) {
     const uint64_t k = base + threadIdx.x;
     bool paired = false;
     if (k < m && ((k - run_start[k]) & 1) == 0 && k + 1 < m && (key2[k + 1] >> 32) == (key2[k] >> 32)) {
-      const uint32_t a = idx[k], b = idx[k + 1];
-      const float wa = cur.w[a], wb = cur.w[b];
-      const uint64_t ia = cur.id[a], ib = cur.id[b];
+      const WeightCand ca = cand[slot[k]], cb = cand[slot[k + 1]];
+      const uint32_t a = ca.index, b = cb.index;
+      const float wa = ca.w, wb = cb.w;
+      const uint64_t ia = ca.id, ib = cb.id;
       const uint4 d = draw(key, ia < ib ? ia : ib, update_index, 0, TAG_WEIGHT);
       const double pa = (double)wa / ((double)wa + (double)wb);
       const float wsum = wa + wb;
@@ -212,8 +243,12 @@ static unsigned blocks_for(uint64_t n) {
 }
 
 hipError_t weight_temp_bytes(uint64_t n, size_t* bytes) {
-  size_t a = 0, b = 0, c = 0;
-  hipError_t e = rocprim::radix_sort_pairs(nullptr, a, (const uint64_t*)nullptr, (uint64_t*)nullptr,
+  size_t a = 0, b = 0, c = 0, d = 0;
+  hipError_t e = rocprim::radix_sort_pairs(nullptr, d, (const uint64_t*)nullptr, (uint64_t*)nullptr,
+                                           rocprim::counting_iterator<uint32_t>(0), (uint32_t*)nullptr, (size_t)n, 0,
+                                           64);
+  if (e != hipSuccess) return e;
+  e = rocprim::radix_sort_pairs(nullptr, a, (const uint64_t*)nullptr, (uint64_t*)nullptr,
                                            (const uint32_t*)nullptr, (uint32_t*)nullptr, (size_t)n, 0, 64);
   if (e != hipSuccess) return e;
   e = rocprim::inclusive_scan(nullptr, b, (const uint32_t*)nullptr, (uint32_t*)nullptr, (size_t)n,
@@ -222,7 +257,7 @@ hipError_t weight_temp_bytes(uint64_t n, size_t* bytes) {
   e = rocprim::exclusive_scan(nullptr, c, (const uint32_t*)nullptr, (uint32_t*)nullptr, 0u, (size_t)n,
                               rocprim::plus<uint32_t>());
   if (e != hipSuccess) return e;
-  *bytes = std::max(a, std::max(b, c));
+  *bytes = std::max(std::max(a, d), std::max(b, c));
   return hipSuccess;
 }
 
@@ -233,32 +268,51 @@ hipError_t launch_weight_update(const Soa& cur, const Soa& out, uint64_t n, cons
   if (e != hipSuccess) return e;
   const uint64_t tiles = (n + kWtTile - 1) / kWtTile;
   hipLaunchKernelGGL(k_wt_classify, dim3((unsigned)(tiles < 8192 ? tiles : 8192)), dim3(kWtBlock), 0, stream, cur, n,
-                     g, rho, W.cls, W.idx0, W.key0, W.key2, W.counters);
+                     g, rho, W.cls, W.cand, W.key2, W.counters);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  unsigned long long m = 0;
-  if ((e = hipMemcpyAsync(&m, W.counters, sizeof(m), hipMemcpyDeviceToHost, stream)) != hipSuccess) return e;
+  unsigned long long counted[4];
+  if ((e = hipMemcpyAsync(counted, W.counters, sizeof(counted), hipMemcpyDeviceToHost, stream)) != hipSuccess)
+    return e;
   if ((e = hipStreamSynchronize(stream)) != hipSuccess) return e;
+  const unsigned long long m = counted[0];
   size_t tb = W.temp_bytes;
   if (m > 1) {
-    // candidates by id (values: slots), then (stable) by cell and energy
-    hipLaunchKernelGGL(k_wt_iota, dim3(blocks_for(m)), dim3(256), 0, stream, W.pos, (uint64_t)m);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    e = rocprim::radix_sort_pairs(W.temp, tb, W.key0, W.key1, W.pos, W.cnt, (size_t)m, 0, 64, stream);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_wt_key2, dim3(blocks_for(m)), dim3(256), 0, stream, W.cnt, (uint64_t)m, W.idx0, W.key2,
-                       W.idx1, W.key0);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    tb = W.temp_bytes;
-    e = rocprim::radix_sort_pairs(W.temp, tb, W.key0, W.key1, W.idx1, W.idx0, (size_t)m, 0, 32 + g.cell_bits,
-                                  stream);
-    if (e != hipSuccess) return e;
+    // Candidates (values: slots) by cell and energy; equal ones by id.  One sort
+    // and k_wt_ties where at most kWtTies candidates of a cell have the same
+    // energy (1.1 ms for some 7e6 candidates); otherwise by id, then (stable) by
+    // the key (2.4 ms), at once where many are at rest, as newly placed ones are.
+    const rocprim::counting_iterator<uint32_t> slots(0);
+    unsigned long long longer = 16 * counted[3] > m;
+    if (!longer) {
+      e = rocprim::radix_sort_pairs(W.temp, tb, W.key2, W.key1, slots, W.idx0, (size_t)m, 0, 32 + g.cell_bits, stream);
+      if (e != hipSuccess) return e;
+      hipLaunchKernelGGL(k_wt_ties, dim3(blocks_for(m)), dim3(256), 0, stream, W.key1, (uint64_t)m, W.cand, W.idx0,
+                         W.counters + 2);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+      if ((e = hipMemcpyAsync(&longer, W.counters + 2, sizeof(longer), hipMemcpyDeviceToHost, stream)) != hipSuccess)
+        return e;
+      if ((e = hipStreamSynchronize(stream)) != hipSuccess) return e;
+    }
+    if (longer) {
+      hipLaunchKernelGGL(k_wt_ids, dim3(blocks_for(m)), dim3(256), 0, stream, W.cand, (uint64_t)m, W.key0);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+      tb = W.temp_bytes;
+      e = rocprim::radix_sort_pairs(W.temp, tb, W.key0, W.key1, slots, W.cnt, (size_t)m, 0, 64, stream);
+      if (e != hipSuccess) return e;
+      hipLaunchKernelGGL(k_wt_key2, dim3(blocks_for(m)), dim3(256), 0, stream, W.cnt, (uint64_t)m, W.key2, W.key0);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+      tb = W.temp_bytes;
+      e = rocprim::radix_sort_pairs(W.temp, tb, W.key0, W.key1, W.cnt, W.idx0, (size_t)m, 0, 32 + g.cell_bits,
+                                    stream);
+      if (e != hipSuccess) return e;
+    }
     hipLaunchKernelGGL(k_wt_heads, dim3(blocks_for(m)), dim3(256), 0, stream, W.key1, (uint64_t)m, W.pos);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     tb = W.temp_bytes;
     e = rocprim::inclusive_scan(W.temp, tb, W.pos, W.idx1, (size_t)m, rocprim::maximum<uint32_t>(), stream);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_wt_pair, dim3(blocks_for(m)), dim3(256), 0, stream, W.key1, W.idx0, W.idx1, (uint64_t)m,
-                       cur, W.cls, key, update_index, W.counters + 1);
+    hipLaunchKernelGGL(k_wt_pair, dim3(blocks_for(m)), dim3(256), 0, stream, W.key1, W.idx0, W.cand, W.idx1,
+                       (uint64_t)m, cur, W.cls, key, update_index, W.counters + 1);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   hipLaunchKernelGGL(k_wt_counts, dim3(blocks_for(n)), dim3(256), 0, stream, W.cls, n, W.cnt);
