@@ -63,6 +63,15 @@ constexpr uint32_t kTagBits = 16;  // groups: at most 4096 swarms
 __device__ __forceinline__ uint32_t tag_of(uint32_t packed) { return packed & ((1u << kTagBits) - 1u); }
 __device__ __forceinline__ uint32_t generation_of(uint32_t packed) { return packed >> kTagBits; }
 
+// First chunks: an even share up to kStaticShare electrons a wave, so that the
+// phase needs no work counter; three quarters of one beyond.  With three
+// quarters always, 4096 waves asked the one counter for the rest of some 70
+// electrons each as soon as a few lanes were free and stood in its queue (64
+// swarms of 4096: 156 us a step, now 97; of 8192 229, now 132; 4e5 streamer
+// electrons 303, now 268); an even share of 290 is 4 % slower than three
+// quarters on the streamer tip, where the waves' electrons differ more.
+constexpr float kStaticShare = 256.0f;
+
 struct WaveStage {
   // newborns as their parent left them: x, y, z, w, birth time; segment
   // number, group and generation, parent id and the newborn's energy (the
@@ -506,13 +515,15 @@ __device__ __forceinline__ void fly_all(bool local, uint32_t quota, uint64_t n, 
   uint32_t src_hint = 0;   // source's hint for the current chunk
   const uint32_t lane = lane_id();
   // First chunks: one per wave, wave w of block b at place w gridDim + b, so
-  // that a short phase spreads over the blocks; three quarters of an even share
-  // of the work (half of one: 27.4 instead of 26.8 ms on the streamer stage), between kChunkMin and the schedule's chunk (a phase that fits one
-  // kChunkMin per wave needs no work counter at all).
+  // that a short phase spreads over the blocks; an even share of the work or
+  // three quarters of one (half of one: 27.4 instead of 26.8 ms on the streamer
+  // stage), between kChunkMin and the schedule's chunk.
   const uint32_t waves = gridDim.x * (blockDim.x >> 6);
+  const float per_wave = __builtin_amdgcn_rcpf((float)waves);  // (a 64-bit division is some 100 instructions)
   uint64_t first;  // electrons in all first chunks together
   {
-    const uint64_t share = 3u * n / (4u * (uint64_t)waves);
+    const float even = (float)n * per_wave;
+    const uint64_t share = (uint64_t)(even <= kStaticShare ? even + 1.0f : 0.75f * even);
     const uint32_t most = chunk.get();
     const uint32_t ch = share < (uint64_t)kChunkMin ? kChunkMin : (share < (uint64_t)most ? (uint32_t)share : most);
     const uint32_t w = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) * gridDim.x + blockIdx.x);
@@ -573,7 +584,7 @@ __device__ __forceinline__ void fly_all(bool local, uint32_t quota, uint64_t n, 
             // 256 swarms 7 % in work-counter atomics (354 against 331 ms for
             // 300 steps, as with fixed chunks).
             const uint32_t most = chunk.get();
-            const uint64_t share = (n - seen) / (uint64_t)waves;
+            const uint64_t share = (uint64_t)((float)(n - seen) * per_wave);
             const uint32_t ch =
                 share < (uint64_t)kChunkMin ? kChunkMin : (share < (uint64_t)most ? (uint32_t)share : most);
             unsigned long long base = 0;

@@ -1,0 +1,27 @@
+"""First chunks of the step kernel's waves at their edges: one smallest chunk a
+wave, an even share up to 256 electrons a wave, three quarters of one beyond.
+With 256 waves and with the default launch the same electrons come out (random
+numbers follow the ids), bit for bit."""
+import numpy as np
+import pytest
+
+from paper_2110_14494_amd import workloads as W
+from test_gpu_schedule import COUNTS, _run, pic  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+WAVES = 256
+
+
+@pytest.mark.parametrize("n", [1, WAVES * 64 - 1, WAVES * 64 + 1, WAVES * 255 + 1, WAVES * 256, WAVES * 256 + 1,
+                               WAVES * 300 + 7])
+def test_first_chunks(pic, n):  # noqa: F811
+    cfg = W.tip_block_config(m=32, n=n)
+    ref, rho_ref, st_ref = _run(pic, cfg, None, steps=2)
+    for s in ({"block": 64, "blocks_per_cu": 1}, {"block": 64, "blocks_per_cu": 1, "chunk": 64}):
+        g, rho, st = _run(pic, cfg, s, steps=2)
+        assert st["launch_grid"] == WAVES and st["launch_block"] == 64
+        for k in COUNTS:
+            assert st[k] == st_ref[k], k
+        assert np.array_equal(rho, rho_ref)
+        for k in ref:
+            assert np.array_equal(g[k], ref[k]), k
