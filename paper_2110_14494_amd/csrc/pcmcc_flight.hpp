@@ -477,6 +477,18 @@ __device__ __forceinline__ int flight_complete(Flight& f, const double3 an, cons
   return ev;
 }
 
+// A wave's place among those of the grid (its first chunk's): wave w of block b
+// at w gridDim + b, with the waves turned by one every gridDim / (waves per
+// block) blocks, so that a SIMD, which takes the same wave of each of its
+// blocks, gets places all over the work (without the turns the SIMDs of the
+// last waves had all the electrons of the strongest fields: 64 swarms of 8192,
+// 200 steps, 26.4 ms, with them 24.0).  The PIC step forms it once, the swarm
+// step, whose registers are fuller, at each phase: 2 to 3 % each.
+__device__ __forceinline__ uint32_t wave_place() {
+  const uint32_t wpb = blockDim.x >> 6, turn = blockIdx.x * wpb / gridDim.x;
+  return __builtin_amdgcn_readfirstlane((((threadIdx.x >> 6) + turn) & (wpb - 1u)) * gridDim.x + blockIdx.x);
+}
+
 // Runs every electron of a source (n of them) through the rest of the step
 // (tables of ROW floats per node, table_row(nproc)),
 // REFILL lanes at a time (see above), `chunk` (a power of two in [kChunkMin,
@@ -501,8 +513,9 @@ __device__ __forceinline__ int flight_complete(Flight& f, const double3 an, cons
 // arguments; `take` is the grid-wide work counter beyond the first chunks
 // (zero before the first wave starts).  cum_ion (nullable) counts ionizations per group.  Every
 // staged entry is written out before the function returns.
-template <int REFILL, int ROW, class Field, class Source, class Finish>
-__device__ __forceinline__ void fly_all(bool local, uint32_t quota, uint64_t n, unsigned long long* take, KArg<uint32_t> chunk, double dt,
+// place(): the wave's among all of the grid (wave_place).
+template <int REFILL, int ROW, class Place, class Field, class Source, class Finish>
+__device__ __forceinline__ void fly_all(bool local, uint32_t quota, const Place& place, uint64_t n, unsigned long long* take, KArg<uint32_t> chunk, double dt,
                                         const Field& F, const Tab& T, const SpeciesView& S, uint32_t step, Cnt& cnt,
                                         const BirthSink& sink, unsigned long long* cum_ion, WaveStage* L,
                                         const Source& source, const Finish& finish) {
@@ -514,10 +527,10 @@ __device__ __forceinline__ void fly_all(bool local, uint32_t quota, uint64_t n, 
   uint32_t chunk_tag = 0;  // finisher's tag of the current chunk
   uint32_t src_hint = 0;   // source's hint for the current chunk
   const uint32_t lane = lane_id();
-  // First chunks: one per wave, wave w of block b at place w gridDim + b, so
-  // that a short phase spreads over the blocks; an even share of the work or
-  // three quarters of one (half of one: 27.4 instead of 26.8 ms on the streamer
-  // stage), between kChunkMin and the schedule's chunk.
+  // First chunks: one per wave, by its place (so that a short phase spreads over
+  // the blocks); an even share of the work or three quarters of one (half of
+  // one: 27.4 instead of 26.8 ms on the streamer stage), between kChunkMin and
+  // the schedule's chunk.
   const uint32_t waves = gridDim.x * (blockDim.x >> 6);
   const float per_wave = __builtin_amdgcn_rcpf((float)waves);  // (a 64-bit division is some 100 instructions)
   uint64_t first;  // electrons in all first chunks together
@@ -526,7 +539,7 @@ __device__ __forceinline__ void fly_all(bool local, uint32_t quota, uint64_t n, 
     const uint64_t share = (uint64_t)(even <= kStaticShare ? even + 1.0f : 0.75f * even);
     const uint32_t most = chunk.get();
     const uint32_t ch = share < (uint64_t)kChunkMin ? kChunkMin : (share < (uint64_t)most ? (uint32_t)share : most);
-    const uint32_t w = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) * gridDim.x + blockIdx.x);
+    const uint32_t w = place();
     first = (uint64_t)ch * waves;
     pool_next = (uint64_t)ch * w;
     pool_end = pool_next + ch < n ? pool_next + ch : n;

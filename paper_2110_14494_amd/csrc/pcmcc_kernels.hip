@@ -389,6 +389,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
   Ctl* ctl = A.ctl;
   if (threadIdx.x < NCNT) s_tot[threadIdx.x] = 0ull;  // first added to after a barrier
   uint32_t gen = 0;  // barriers so far
+  const uint32_t my_place = wave_place();
+  auto place = [&]() { return my_place; };
   auto none = [](uint32_t*) {};
   // words of the last barrier, wave-uniform
   auto word = [&](int q) { return __builtin_amdgcn_readfirstlane(s_pub[q]); };
@@ -418,7 +420,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
       const KeepInPlace fin{grid_k, nxt_k, A.holes, &ctl->holes.v, ev_k, ring,
                             PlaceNewborn{grid_k, nxt_k, A.holes, 0, n_cur, A.cap, &ctl->child.v, &ctl->overflow.v, ev_k}};
       ring->reset();
-      fly_all<REFILL, ROW>(local, quota, n_cur, &ctl->take[0].v, chunk_k, A.dt, F, T, A.S, step, cnt, sink, nullptr, L, src,
+      fly_all<REFILL, ROW>(local, quota, place, n_cur, &ctl->take[0].v, chunk_k, A.dt, F, T, A.S, step, cnt, sink, nullptr, L, src,
                                  fin);
     }
     grid_barrier(&ctl->bar, gen, s_pub, [&](uint32_t* v) { step_advance(A, v, 0, n_cur, local); });
@@ -430,7 +432,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
       const BirthSink sink{{&ka->pend[(g + 1) & 1]}, &ctl->pend[(g + 1) & 1].v, A.pend_cap, &ctl->overflow.v, 0u, ev_k};
       const PendSource src{{&ka->pend[g & 1]}, kSrcBorn + 1u + (uint32_t)g};
       const PlaceNewborn fin{grid_k, nxt_k, A.holes, h, n_cur, A.cap, &ctl->child.v, &ctl->overflow.v, ev_k};
-      fly_all<REFILL, ROW>(local, quota, np, &ctl->take[(g + 1) & 1].v, chunk_k, A.dt, F, T, A.S, step, cnt, sink, nullptr, L,
+      fly_all<REFILL, ROW>(local, quota, place, np, &ctl->take[(g + 1) & 1].v, chunk_k, A.dt, F, T, A.S, step, cnt, sink, nullptr, L,
                                  src, fin);
       grid_barrier(&ctl->bar, gen, s_pub, [&](uint32_t* v) { step_advance(A, v, g + 1, n_cur, local); });
     }

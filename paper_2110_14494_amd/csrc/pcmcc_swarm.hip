@@ -379,7 +379,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) void k_
     {
       const BirthSink sink{{&ka->pend[0]}, &ctl->pend[0].v, A.pend_cap, &ctl->overflow.v, 0u, no_events};
       const SwarmLoad src{cur_k, base_l, prefix, pck, S, A.key, step, sink, &psteps};
-      fly_all<REFILL, ROW>(true, quota, (uint64_t)prefix[S], &ctl->take[0].v, chunk_k, (double)A.dt, F, T, A.S, step, cnt, sink,
+      fly_all<REFILL, ROW>(true, quota, wave_place, (uint64_t)prefix[S], &ctl->take[0].v, chunk_k, (double)A.dt, F, T, A.S, step, cnt, sink,
                       A.cum_ion, L, src, fin);
     }
     grid_barrier(&ctl->bar, gen, s_pub, [&](uint32_t* v) { swarm_advance(A, v, 0, sample); });
@@ -390,7 +390,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) void k_
       const BirthSink sink{{&ka->pend[(g + 1) & 1]}, &ctl->pend[(g + 1) & 1].v, A.pend_cap, &ctl->overflow.v, 0u,
                            no_events};
       const SwarmPend src{{&ka->pend[g & 1]}};
-      fly_all<REFILL, ROW>(true, quota, np, &ctl->take[(g + 1) & 1].v, chunk_k, (double)A.dt, F, T, A.S, step, cnt, sink,
+      fly_all<REFILL, ROW>(true, quota, wave_place, np, &ctl->take[(g + 1) & 1].v, chunk_k, (double)A.dt, F, T, A.S, step, cnt, sink,
                                   A.cum_ion, L, src, fin);
       grid_barrier(&ctl->bar, gen, s_pub, [&](uint32_t* v) { swarm_advance(A, v, g + 1, sample); });
     }
