@@ -185,12 +185,12 @@ int pcmcc_push_collide_deposit(pcmcc_ctx* ctx, const pcmcc_particles* p, const p
 typedef struct pcmcc_schedule {
   int block;          /* threads per block: 64, 128, 256 or 512; 0 = the size with the most resident waves per
                          compute unit (ties: the larger block), or 64 for a call that starts with fewer than
-                         2^17 particles */
-  int blocks_per_cu;  /* persistent blocks per compute unit; 0 = as many as fit (1 with the 64-thread default of a
-                         small call) */
+                         2^14 particles (2^17 with blocks_per_cu above 1) */
+  int blocks_per_cu;  /* persistent blocks per compute unit; 0 = as many as fit (1 with the default block of a call
+                         that starts with fewer than 2^17 particles) */
   int refill_min;     /* free lanes of a wave that trigger a finish-and-refill batch: 16, 24 or 32; 0 = 24 */
   int chunk;          /* electrons a wave takes from the work counter at a time: a power of two in [64, 4096];
-                         0 = 512 (64 for a call that starts with fewer than 2^17 particles) */
+                         0 = 512 (64 where the block defaults to 64) */
 } pcmcc_schedule;
 
 /* Sets the schedule of later steps on ctx (s NULL: all defaults).

@@ -169,11 +169,12 @@ int resolve_launch(pcmcc_ctx* c, const pcmcc_schedule& s, size_t (*lds)(const Ta
   const int rc = check_schedule(c, s);
   if (rc) return rc;
   const bool small = n_hint > 0 && n_hint < kSmallPopulation && !s.block;
+  const bool one_wave = small && (n_hint < kOneWavePopulation || s.blocks_per_cu > 1);
   const int refill = s.refill_min ? s.refill_min : 24;
-  const int chunk = s.chunk ? s.chunk : (small ? 64 : 512);
+  const int chunk = s.chunk ? s.chunk : (one_wave ? 64 : 512);
   int block = 0, per_cu = 0;
   for (int b : {512, 256, 128, 64}) {
-    if ((s.block && b != s.block) || (small && b != 64)) continue;
+    if ((s.block && b != s.block) || (one_wave && b != 64)) continue;
     int k = 0;
     HIP_TRY(c, occ(b, refill, table_row(T.nproc), lds(T, S, b), &k));
     if (k >= 1 && k * b > per_cu * block) {  // most resident waves; ties keep the larger block

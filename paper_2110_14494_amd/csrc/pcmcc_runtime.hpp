@@ -171,10 +171,14 @@ inline size_t swarm_lds_bytes_s(const TableView& T, int S, int block) { return s
 // lds(block): dynamic LDS bytes of the kernel at that block size; occ(block,
 // refill, lds, &per_cu) its occupancy query.
 // n_hint (0: none) is the start population of a step call: below
-// kSmallPopulation electrons the unset fields default to one 64-thread block
-// per CU and chunks of 64, since grid barriers over fewer, smaller blocks
-// cost less and a small population fills few waves anyway.
-constexpr uint64_t kSmallPopulation = 1u << 17;
+// kSmallPopulation electrons the unset fields default to one block per CU,
+// since a grid barrier over fewer blocks costs less and the population fills
+// few waves anyway; below kOneWavePopulation to blocks of one wave, whose start
+// is the shortest, and chunks of 64.  One block of 64 or of 512 threads, us a
+// call: 1e4 electrons in a uniform field (100 steps) 3604, 3632; in a streamer
+// tip's (6 steps) 12000 824, 801; 30000 1062, 846; 60000 1325, 899; 125000 1904,
+// 1025 (two blocks of 512: 912, 955 and 1052 for the last three).
+constexpr uint64_t kSmallPopulation = 1u << 17, kOneWavePopulation = 1u << 14;
 int resolve_launch(pcmcc_ctx* c, const pcmcc_schedule& s, size_t (*lds)(const TableView&, int, int),
                    hipError_t (*occ)(int, int, int, size_t, int*), const TableView& T, int S, StepLaunch* out,
                    uint64_t n_hint = 0);

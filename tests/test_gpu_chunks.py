@@ -25,3 +25,21 @@ def test_first_chunks(pic, n):  # noqa: F811
         assert np.array_equal(rho, rho_ref)
         for k in ref:
             assert np.array_equal(g[k], ref[k]), k
+
+
+@pytest.mark.parametrize("n,block", [(2 ** 14 - 1, 64), (2 ** 14, None), (2 ** 17 - 1, None), (2 ** 17, None)])
+def test_default_launch_of_small_populations(pic, n, block):  # noqa: F811
+    cfg = W.tip_block_config(m=32, n=n)
+    ref, rho_ref, st_ref = _run(pic, cfg, {"block": 64, "blocks_per_cu": 1}, steps=2)
+    for s in (None, {"blocks_per_cu": 2}):  # the second keeps a block that fits twice
+        g, rho, st = _run(pic, cfg, s, steps=2)
+        if s is None:
+            assert st["launch_block"] == block if block else st["launch_block"] > 64
+            assert (st["launch_grid"] == WAVES) == (n < 2 ** 17)
+        elif n < 2 ** 17:
+            assert st["launch_block"] == 64 and st["launch_grid"] == 2 * WAVES
+        for k in COUNTS:
+            assert st[k] == st_ref[k], k
+        assert np.array_equal(rho, rho_ref)
+        for k in ref:
+            assert np.array_equal(g[k], ref[k]), k
