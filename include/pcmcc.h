@@ -265,7 +265,8 @@ typedef struct pcmcc_swarm_opts {
   int cap_factor;          /* slots per swarm = cap_factor * n0, >= 4 */
   int population_control;  /* 1 on, 0 off */
   int block;               /* threads per block: 64, 128, 256, 512; 0 = tuned or default */
-  int blocks_per_cu;       /* persistent blocks per compute unit; 0 = tuned or default */
+  int blocks_per_cu;       /* persistent blocks per compute unit; 0 = tuned or default (with the default block: 1 for
+                              up to 2^18 electrons under population control) */
   int autotune;            /* 1: time the candidate shapes on this input and keep the fastest */
   const char* tune_cache;  /* JSON file the tuned shapes are read from and written to, or NULL */
   int refill_min;          /* as pcmcc_schedule; 0 = tuned or 24 */

@@ -80,8 +80,20 @@ int pcmcc_swarm_batch(pcmcc_ctx* c, int n_swarms, const double* EN_Td, const int
     if (!want.chunk) want.chunk = t[3];
     if (check_schedule(c, want)) want = pcmcc_schedule{opts->block, opts->blocks_per_cu, opts->refill_min, opts->chunk};
   }
+  // One block per CU by default for up to kFewSwarmElectrons at the start that
+  // population control keeps from growing: the grid barrier and the start over
+  // half the blocks are shorter than what a second one saves (one block of 512
+  // and two, 200 steps, ms: 1 swarm of 100 6.6, 7.2; 8 of 1000 8.2, 8.8; 64 of 700
+  // 9.9, 11.4; 64 of 2500 13.8, 15.2; 64 of 4096 18.3, 18.5; 96 of 8192 35.0, 31.5).
+  constexpr uint64_t kFewSwarmElectrons = 1u << 18;
+  const bool few = opts->population_control && slots / (uint64_t)opts->cap_factor <= kFewSwarmElectrons;
   auto resolve = [&](const pcmcc_schedule& s, StepLaunch* L) {
-    return resolve_launch(c, s, swarm_lds_bytes_s, occupancy_swarm_steps, T, S, L);
+    const int r = resolve_launch(c, s, swarm_lds_bytes_s, occupancy_swarm_steps, T, S, L);
+    if (r == PCMCC_OK && few && !s.block && !s.blocks_per_cu) {
+      L->bpc = 1;
+      L->grid = c->num_cu;
+    }
+    return r;
   };
   rc = ensure_swarm(c, S, slots, J);
   if (rc) return rc;

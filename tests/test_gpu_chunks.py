@@ -43,3 +43,21 @@ def test_default_launch_of_small_populations(pic, n, block):  # noqa: F811
         assert np.array_equal(rho, rho_ref)
         for k in ref:
             assert np.array_equal(g[k], ref[k]), k
+
+
+@pytest.mark.parametrize("n0,blocks", [((700,) * 5, 1), ((2 ** 17, 2 ** 17), 1), ((2 ** 17, 2 ** 17 + 1), None)])
+def test_default_launch_of_few_swarm_electrons(pic, n0, blocks):  # noqa: F811
+    EN = np.linspace(60.0, 400.0, len(n0))
+    out = []
+    with pic.Context(0) as ctx:
+        ctx.setup(W.electron_species(), W.air_like_tables())
+        for launch in ({}, {"block": 512, "blocks_per_cu": 2}):
+            print(f"[gpu] swarms {n0[:2]} {launch}", flush=True)
+            rc, val, err, st, mom, cnt = pic.swarm_batch(ctx, EN, np.array(n0), 1e-12, 40, 3, sample_every=10, n_batches=2,
+                                                         raw=True, **launch)
+            assert rc == 0
+            out.append((mom, cnt, st))
+    if blocks:
+        assert out[0][2]["launch_grid"] == blocks * WAVES
+    for k in range(2):
+        assert np.array_equal(np.asarray(out[0][k]), np.asarray(out[1][k]))
