@@ -291,8 +291,15 @@ __device__ __forceinline__ void swarm_commit(const SwarmArgs& A, uint32_t* v) {
   }
 }
 
+// An overflow ends the step here: a swarm's count then runs past its region of
+// the buffer (a survivor that found no slot is counted too), so neither a
+// newborn generation nor a sample may follow.
 __device__ __forceinline__ void swarm_advance(const SwarmArgs& A, uint32_t* v, int p, bool sample) {
   SwarmCtl* ctl = A.ctl;
+  if (ld_relaxed(&ctl->overflow.v)) {
+    swarm_commit(A, v);
+    return;
+  }
   const uint64_t np = ld_relaxed(&ctl->pend[p & 1].v);
   if (np > 0 && p < kMaxGenerations) {
     st_relaxed(&ctl->take[p & 1].v, 0ull);
@@ -302,7 +309,7 @@ __device__ __forceinline__ void swarm_advance(const SwarmArgs& A, uint32_t* v, i
     return;
   }
   if (np > 0) atomicOr(&ctl->overflow.v, OVF_LIMIT);
-  if (sample) {
+  if (np == 0 && sample) {
     v[0] = SWARM_SAMPLE;
     return;
   }
