@@ -397,11 +397,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
   int sel = __builtin_amdgcn_readfirstlane(ctl->cur_sel);
   uint32_t n_cur = __builtin_amdgcn_readfirstlane((uint32_t)ctl->n_cur);  // capacity below 2^32
   bool local = true;
-  // Newborns a wave may run itself in a phase: an even share of 64 full
-  // queues, the most that the queue would let through, and some.
-  const uint32_t quota = (uint32_t)min((unsigned long long)(A.pend_cap * kMaxGenerations) /
-                                               (gridDim.x * (blockDim.x >> 6)) + 4096ull,
-                                       0xFFFFFFFFull);
+  const uint32_t quota = newborn_quota(A.pend_cap, 4096);
 
   for (int s = 0; s < A.n_steps;) {
     const KArg<Soa> cur_k{&ka->buf[sel]}, nxt_k{&ka->buf[sel ^ 1]};

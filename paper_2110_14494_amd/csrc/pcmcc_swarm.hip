@@ -275,9 +275,8 @@ __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
 // waits for one block to commit the swarms one by one.
 enum SwarmCode : uint32_t { SWARM_NEWBORN = 0, SWARM_SAMPLE = 1, SWARM_DONE = 2, SWARM_REJECTED = 3 };
 
-__device__ __forceinline__ void swarm_commit(const SwarmArgs& A, uint32_t* v) {
+__device__ __forceinline__ void swarm_commit(const SwarmArgs& A, uint32_t* v, unsigned of) {
   SwarmCtl* ctl = A.ctl;
-  const unsigned of = ld_relaxed(&ctl->overflow.v);
   if (of) {
     ctl->status = (of & OVF_LIMIT) ? PCMCC_ELIMIT : PCMCC_ECAPACITY;
     v[0] = SWARM_REJECTED;
@@ -296,24 +295,22 @@ __device__ __forceinline__ void swarm_commit(const SwarmArgs& A, uint32_t* v) {
 // newborn generation nor a sample may follow.
 __device__ __forceinline__ void swarm_advance(const SwarmArgs& A, uint32_t* v, int p, bool sample) {
   SwarmCtl* ctl = A.ctl;
-  if (ld_relaxed(&ctl->overflow.v)) {
-    swarm_commit(A, v);
-    return;
-  }
+  unsigned of = ld_relaxed(&ctl->overflow.v);
   const uint64_t np = ld_relaxed(&ctl->pend[p & 1].v);
-  if (np > 0 && p < kMaxGenerations) {
-    st_relaxed(&ctl->take[p & 1].v, 0ull);
-    st_relaxed(&ctl->pend[(p & 1) ^ 1].v, 0ull);
-    v[0] = SWARM_NEWBORN;
-    v[1] = (uint32_t)(np < A.pend_cap ? np : A.pend_cap);
-    return;
+  if (np > 0 && of == 0) {
+    if (p < kMaxGenerations) {
+      st_relaxed(&ctl->take[p & 1].v, 0ull);
+      st_relaxed(&ctl->pend[(p & 1) ^ 1].v, 0ull);
+      v[0] = SWARM_NEWBORN;
+      v[1] = (uint32_t)(np < A.pend_cap ? np : A.pend_cap);
+      return;
+    }
+    of = OVF_LIMIT;
   }
-  if (np > 0) atomicOr(&ctl->overflow.v, OVF_LIMIT);
-  if (np == 0 && sample) {
+  if (of == 0 && sample)
     v[0] = SWARM_SAMPLE;
-    return;
-  }
-  swarm_commit(A, v);
+  else
+    swarm_commit(A, v, of);
 }
 
 template <int BS, int REFILL, int ROW>
@@ -354,9 +351,9 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) void k_
   const unsigned lane = lane_id();
   const uint32_t wpb = BS / 64;
   SwarmCtl* ctl = A.ctl;
-  // Newborns a wave may run itself in a phase: 64 full queues, the most that
-  // the queue would let through.
-  const uint32_t quota = (uint32_t)min((unsigned long long)(A.pend_cap * kMaxGenerations), 0xFFFFFFFFull);
+  // Beyond the even share a wave may fill every slot: a swarm step is not run
+  // again through the queue.
+  const uint32_t quota = newborn_quota(A.pend_cap, 4 * A.pend_cap);
   uint32_t gen = 0;  // barriers so far
   auto word = [&](int q) { return __builtin_amdgcn_readfirstlane(s_pub[q]); };
 
@@ -492,7 +489,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) void k_
         unsigned long long* dst = A.mom + (((size_t)cur_s * A.n_samples + j) * kNMom + threadIdx.x) * 2;
         add128_atomic(dst, acc_lo[threadIdx.x], acc_hi[threadIdx.x]);
       }
-      grid_barrier(&ctl->bar, gen, s_pub, [&](uint32_t* v) { swarm_commit(A, v); });
+      grid_barrier(&ctl->bar, gen, s_pub, [&](uint32_t* v) { swarm_commit(A, v, ld_relaxed(&ctl->overflow.v)); });
     }
     if (word(0) == SWARM_REJECTED) break;
 #pragma unroll
