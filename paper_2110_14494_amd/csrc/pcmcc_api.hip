@@ -39,9 +39,9 @@ int pcmcc_create(pcmcc_ctx** out, int device, void* hip_stream) {
       return fail(nullptr, PCMCC_EHIP, "hipEventCreate failed");
     }
   }
-  if (dalloc(&c->ctl, 1) != hipSuccess || dalloc(&c->emax_bits, 1) != hipSuccess ||
+  if (hipMalloc((void**)&c->ctl, sizeof(Ctl) + kCtlTail) != hipSuccess || dalloc(&c->emax_bits, 1) != hipSuccess ||
       dalloc(&c->dep_err, 1) != hipSuccess ||
-      hipHostMalloc((void**)&c->host_ctl, sizeof(Ctl), hipHostMallocDefault) != hipSuccess ||
+      hipHostMalloc((void**)&c->host_ctl, sizeof(Ctl) + kCtlTail, hipHostMallocDefault) != hipSuccess ||
       hipHostMalloc((void**)&c->host_n, sizeof(int64_t), hipHostMallocDefault) != hipSuccess ||
       hipHostMalloc((void**)&c->host_err, sizeof(unsigned), hipHostMallocDefault) != hipSuccess) {
     pcmcc_destroy(c);

@@ -138,22 +138,32 @@ int pcmcc_mlp_train(pcmcc_ctx* c, const float* params_in, int64_t n, const float
 }
 
 // Device memory for a call's parameters, flags and table and the pinned copy
-// they are sent from, kept by the context up to kInferKeep (a call's kernel
-// has ended when the call returns, so the next may overwrite both): with three
-// allocations, uploads from pageable memory and frees a call of 1000 points
-// took 54.5 us, with these 35.2 us.  A larger call's are given back by the
-// next one that is not.
+// they are sent from (a call's kernel has ended when the call returns, so the
+// next may overwrite both).  Up to kCtlTail bytes they lie behind the context's
+// control block: with three allocations, uploads from pageable memory and frees a
+// call of 1000 points with a table of 2048 nodes took 66 us and a context's first
+// 69, with these 34 and 38 (63 with memory of their own, taken on that call).
+// Larger ones are taken when they are first needed and kept up to kInferKeep; what
+// a call takes beyond that, the next one that does not gives back (table of
+// 200000 nodes: 194 us against 226, a context's first call 290 against 240).
 constexpr size_t kInferKeep = (size_t)4 << 20;
-static hipError_t infer_space(pcmcc_ctx* c, size_t bytes) {
-  if (bytes <= c->infer_bytes && (c->infer_bytes <= kInferKeep || bytes > kInferKeep)) return hipSuccess;
-  dfree(c->infer_dev);
-  if (c->infer_host) (void)hipHostFree(c->infer_host);
-  c->infer_dev = c->infer_host = nullptr;
-  c->infer_bytes = 0;
-  const size_t want = std::max(bytes, (size_t)64 << 10);
-  hipError_t e = dalloc(&c->infer_dev, want);
-  if (e == hipSuccess) e = hipHostMalloc((void**)&c->infer_host, want, hipHostMallocDefault);
-  if (e == hipSuccess) c->infer_bytes = want;
+static hipError_t infer_space(pcmcc_ctx* c, size_t bytes, uint8_t** dev, uint8_t** host) {
+  hipError_t e = hipSuccess;
+  const bool small = bytes <= kCtlTail;
+  if (small ? c->infer_bytes > kInferKeep
+            : bytes > c->infer_bytes || (c->infer_bytes > kInferKeep && bytes <= kInferKeep)) {
+    dfree(c->infer_dev);
+    if (c->infer_host) (void)hipHostFree(c->infer_host);
+    c->infer_dev = c->infer_host = nullptr;
+    c->infer_bytes = 0;
+    if (!small) {
+      e = dalloc(&c->infer_dev, bytes);
+      if (e == hipSuccess) e = hipHostMalloc((void**)&c->infer_host, bytes, hipHostMallocDefault);
+      if (e == hipSuccess) c->infer_bytes = bytes;
+    }
+  }
+  *dev = small ? (uint8_t*)(c->ctl + 1) : c->infer_dev;
+  *host = small ? (uint8_t*)(c->host_ctl + 1) : c->infer_host;
   return e;
 }
 
@@ -174,19 +184,20 @@ int pcmcc_mlp_infer(pcmcc_ctx* c, const float* params, const pcmcc_mlp_infer_opt
   const size_t b_tab = o->n_cells > 0 ? sizeof(float) * (size_t)o->n_nodes * PCMCC_MLP_OUT : 0;
   const size_t at_mask = padded(b_par), at_tab = at_mask + padded(b_mask), bytes = at_tab + b_tab;
   InferArgs A{};
-  hipError_t e = infer_space(c, bytes);
+  uint8_t *dev = nullptr, *host = nullptr;
+  hipError_t e = infer_space(c, bytes, &dev, &host);
   if (e == hipSuccess) {
-    std::memcpy(c->infer_host, params, b_par);
+    std::memcpy(host, params, b_par);
     if (o->n_cells > 0) {
-      std::memcpy(c->infer_host + at_mask, o->fallback, b_mask);
-      std::memcpy(c->infer_host + at_tab, o->table, b_tab);
+      std::memcpy(host + at_mask, o->fallback, b_mask);
+      std::memcpy(host + at_tab, o->table, b_tab);
     }
-    e = hipMemcpyAsync(c->infer_dev, c->infer_host, bytes, hipMemcpyHostToDevice, c->stream);
+    e = hipMemcpyAsync(dev, host, bytes, hipMemcpyHostToDevice, c->stream);
   }
   if (e != hipSuccess) return fail(c, PCMCC_EHIP, "surrogate upload: %s", hipGetErrorString(e));
-  const float* dparams = (const float*)c->infer_dev;
-  const uint8_t* dmask = c->infer_dev + at_mask;
-  const float* dtable = (const float*)(c->infer_dev + at_tab);
+  const float* dparams = (const float*)dev;
+  const uint8_t* dmask = dev + at_mask;
+  const float* dtable = (const float*)(dev + at_tab);
   A.params = dparams;
   A.EN = EN_dev;
   A.out = out_dev;

@@ -1,0 +1,65 @@
+"""A context's first surrogate evaluation takes no memory of its own: it may
+cost little more than the next one.  An allocation on the device and one of
+pinned host memory on that call cost some 28 us, either alone 10 us or more;
+the medians over 25 contexts may differ by 10 us.  Descriptions of growing
+and shrinking size in one context give what a fresh context gives."""
+import time
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2110_14494_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+LO, HI = np.log(10.0), np.log(1000.0)
+
+
+def _norm(cells, nodes):
+    from paper_2110_14494_amd import surrogate as S
+    rng = np.random.default_rng(nodes)
+    nm = S.Norm()
+    nm.opts.mu_x, nm.opts.sd_x = 0.5 * (LO + HI), 1.3
+    nm.opts.mu_y[:], nm.opts.sd_y[:] = [0.5] * 6, [2.0] * 6
+    return nm.with_fallback(rng.integers(0, 64, cells).astype(np.uint8), LO, HI,
+                            rng.normal(size=(nodes, 6)).astype(np.float32), LO, HI)
+
+
+@pytest.fixture(scope="module")
+def inputs():
+    EN = torch.from_numpy(W.log_uniform_EN(1000, 3)).cuda()
+    return W.mlp_init(2).astype(np.float32), EN
+
+
+def test_first_call_of_a_context(inputs):
+    from paper_2110_14494_amd import pic, surrogate as S
+    params, EN = inputs
+    out, nm, first, second = torch.empty((6, 1000), device="cuda"), _norm(256, 2048), [], []
+    print("[gpu] first surrogate call of 26 contexts", flush=True)
+    for _ in range(26):
+        with pic.Context(0) as ctx:
+            t = [time.perf_counter()]
+            for _ in range(2):
+                S.infer(ctx, params, nm, EN, out)
+                t.append(time.perf_counter())
+        first.append(t[1] - t[0])
+        second.append(t[2] - t[1])
+    a, b = (1e6 * float(np.median(v[1:])) for v in (first, second))  # (the first loads the kernel)
+    print(f"[gpu] first {a:.1f} us, second {b:.1f} us", flush=True)
+    assert a <= b + 10.0
+
+
+def test_descriptions_of_any_size_in_turn(inputs):
+    """Behind the control block, in kept memory (above 512 KiB), beyond what is
+    kept (4 MiB), and back."""
+    from paper_2110_14494_amd import pic, surrogate as S
+    params, EN = inputs
+    sizes = [(256, 2048), (64, 30000), (5000, 2048), (300, 200000), (64, 30000), (1, 2), (524288 - 18944, 2)]
+    with pic.Context(0) as one:
+        for cells, nodes in sizes:
+            print(f"[gpu] surrogate description {cells} {nodes}", flush=True)
+            nm = _norm(cells, nodes)
+            got, _ = S.infer(one, params, nm, EN)
+            with pic.Context(0) as ctx:
+                want, _ = S.infer(ctx, params, nm, EN)
+            assert torch.equal(got, want)
