@@ -209,6 +209,13 @@ __global__ void k_wt_pair(const uint64_t* __restrict__ key2, const uint32_t* __r
   if (lane_id() == 0 && pairs) atomicAdd(n_pairs, pairs);
 }
 
+// The candidates' weights as k_wt_classify found them (an update that does not
+// fit leaves the particles as they were).
+__global__ void k_wt_restore(const WeightCand* __restrict__ cand, uint64_t m, float* __restrict__ w) {
+  for (uint64_t k = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; k < m; k += (uint64_t)gridDim.x * blockDim.x)
+    w[cand[k].index] = cand[k].w;
+}
+
 __global__ void k_wt_counts(const uint8_t* __restrict__ cls, uint64_t n, uint32_t* __restrict__ cnt) {
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
     const uint8_t c = cls[i];
@@ -331,7 +338,10 @@ hipError_t launch_weight_update(const Soa& cur, const Soa& out, uint64_t n, cons
   *n_out = total;
   *pairs_out = pairs;
   *splits_out = total - (n - pairs);  // n - pairs kept or split, each split adds one
-  if (total > g.capacity) return hipSuccess;  // the caller reports the capacity; nothing written
+  if (total > g.capacity) {  // the caller reports the capacity
+    if (m > 0) hipLaunchKernelGGL(k_wt_restore, dim3(blocks_for(m)), dim3(256), 0, stream, W.cand, (uint64_t)m, cur.w);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_wt_emit, dim3(blocks_for(n)), dim3(256), 0, stream, cur, out, n, W.cls, W.pos, key,
                      update_index);
   return hipGetLastError();
