@@ -70,7 +70,6 @@ int pcmcc_destroy(pcmcc_ctx* c) {
   dfree(c->wt.cls);
   dfree(c->wt.cand);
   dfree(c->wt.idx0);
-  dfree(c->wt.key0);
   dfree(c->wt.key1);
   dfree(c->wt.key2);
   dfree(c->wt.cnt);

@@ -156,10 +156,10 @@ struct WeightWork {
   uint8_t* cls;                 // [n] class per particle
   WeightCand* cand;             // [n] candidates by slot
   uint32_t* idx0;               // [n] sorted slots
-  uint64_t *key0, *key1;        // [n] sort keys
+  uint64_t* key1;               // [n] sorted keys
   uint64_t* key2;               // [n] candidates' (cell, energy) keys by slot
   uint32_t* cnt;                // [n] output counts
-  uint32_t *idx1, *pos;         // [n] run starts and positions, in key0's memory (used after the sorts)
+  uint32_t *idx1, *pos;         // [n] run starts and positions, in key2's memory (used after the sorts)
   unsigned long long* counters;  // [4] candidates, merged pairs, long run of equal keys, candidates at rest
   void* temp;
   size_t temp_bytes;

@@ -385,13 +385,13 @@ int run_deposit(pcmcc_ctx* c, const float* x, const float* y, const float* z, co
   return check ? deposit_range_check(c) : PCMCC_OK;
 }
 
-// Buffers of the weight update for n particles on `ncell` cells.
+// Buffers of the weight update for n particles on `ncell` cells (41 B a
+// particle and the sort's; a context's first update pays for them).
 int ensure_weights(pcmcc_ctx* c, uint64_t n, size_t ncell) {
   if (c->wt_n < n) {
     dfree(c->wt.cls);
     dfree(c->wt.cand);
     dfree(c->wt.idx0);
-    dfree(c->wt.key0);
     dfree(c->wt.key1);
     dfree(c->wt.key2);
     dfree(c->wt.cnt);
@@ -404,14 +404,14 @@ int ensure_weights(pcmcc_ctx* c, uint64_t n, size_t ncell) {
     size_t tb = 0;
     HIP_TRY(c, weight_temp_bytes(n, &tb));
     if (dalloc(&c->wt.cls, n) != hipSuccess || dalloc(&c->wt.cand, n) != hipSuccess ||
-        dalloc(&c->wt.idx0, n) != hipSuccess || dalloc(&c->wt.key0, n) != hipSuccess ||
+        dalloc(&c->wt.idx0, n) != hipSuccess ||
         dalloc(&c->wt.key1, n) != hipSuccess || dalloc(&c->wt.key2, n) != hipSuccess ||
         dalloc(&c->wt.cnt, n) != hipSuccess || dalloc(&c->wt.counters, 4) != hipSuccess ||
         hipMalloc(&c->wt.temp, std::max<size_t>(tb, 16)) != hipSuccess) {
       (void)hipGetLastError();
       return fail(c, PCMCC_ENOMEM, "cannot allocate weight-update buffers for %llu particles", (unsigned long long)n);
     }
-    c->wt.idx1 = (uint32_t*)c->wt.key0;
+    c->wt.idx1 = (uint32_t*)c->wt.key2;
     c->wt.pos = c->wt.idx1 + n;
     c->wt.temp_bytes = std::max<size_t>(tb, 16);
     c->wt_n = n;

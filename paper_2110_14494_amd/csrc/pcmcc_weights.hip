@@ -301,15 +301,16 @@ hipError_t launch_weight_update(const Soa& cur, const Soa& out, uint64_t n, cons
       if ((e = hipStreamSynchronize(stream)) != hipSuccess) return e;
     }
     if (longer) {
-      hipLaunchKernelGGL(k_wt_ids, dim3(blocks_for(m)), dim3(256), 0, stream, W.cand, (uint64_t)m, W.key0);
+      uint64_t* const key0 = out.id;  // written by k_wt_emit only: at least m words of scratch until then
+      hipLaunchKernelGGL(k_wt_ids, dim3(blocks_for(m)), dim3(256), 0, stream, W.cand, (uint64_t)m, key0);
       if ((e = hipGetLastError()) != hipSuccess) return e;
       tb = W.temp_bytes;
-      e = rocprim::radix_sort_pairs(W.temp, tb, W.key0, W.key1, slots, W.cnt, (size_t)m, 0, 64, stream);
+      e = rocprim::radix_sort_pairs(W.temp, tb, key0, W.key1, slots, W.cnt, (size_t)m, 0, 64, stream);
       if (e != hipSuccess) return e;
-      hipLaunchKernelGGL(k_wt_key2, dim3(blocks_for(m)), dim3(256), 0, stream, W.cnt, (uint64_t)m, W.key2, W.key0);
+      hipLaunchKernelGGL(k_wt_key2, dim3(blocks_for(m)), dim3(256), 0, stream, W.cnt, (uint64_t)m, W.key2, key0);
       if ((e = hipGetLastError()) != hipSuccess) return e;
       tb = W.temp_bytes;
-      e = rocprim::radix_sort_pairs(W.temp, tb, W.key0, W.key1, W.cnt, W.idx0, (size_t)m, 0, 32 + g.cell_bits,
+      e = rocprim::radix_sort_pairs(W.temp, tb, key0, W.key1, W.cnt, W.idx0, (size_t)m, 0, 32 + g.cell_bits,
                                     stream);
       if (e != hipSuccess) return e;
     }
