@@ -374,7 +374,7 @@ __device__ __forceinline__ void step_advance(const PicArgs& A, uint32_t* v, int 
 
 template <int REFILL, int ROW>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k_pic_steps(PicArgs A) {
-  extern __shared__ float smem[];
+  extern __shared__ __align__(16) float smem[];
   __shared__ uint32_t s_pub[kBarWords];
   __shared__ unsigned long long s_tot[NCNT];  // counters of the committed steps
   const Tab T = stage_tables(A.T, A.S, smem);
@@ -871,7 +871,7 @@ __global__ void k_philox(const uint4* __restrict__ ctr, Key key, uint4* __restri
 // Table lookups exactly as the step kernel does them (LDS-staged tables).
 __global__ void k_lookup(TableView TV, SpeciesView S, const float* __restrict__ eps, float* __restrict__ cum,
                          const float* __restrict__ s_ub, float* __restrict__ maj, int64_t n) {
-  extern __shared__ float smem[];
+  extern __shared__ __align__(16) float smem[];
   const Tab T = stage_tables(TV, S, smem);
   for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < n; q += (int64_t)gridDim.x * blockDim.x) {
     const float e = eps[q];

@@ -315,7 +315,7 @@ __device__ __forceinline__ void swarm_advance(const SwarmArgs& A, uint32_t* v, i
 
 template <int BS, int REFILL, int ROW>
 __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) void k_swarm_steps(SwarmArgs A) {
-  extern __shared__ float smem[];
+  extern __shared__ __align__(16) float smem[];
   __shared__ uint32_t s_pub[kBarWords];
   __shared__ unsigned long long s_tot[NCNT + 1];  // counters of the committed steps, then the particle-steps
   const Tab T = stage_tables(A.T, A.S, smem);
