@@ -172,8 +172,12 @@ int pcmcc_init_tables(pcmcc_ctx* ctx, int n_e, double eps_min_eV, double eps_max
  *            (2^31 electrons per cell); otherwise PCMCC_ERANGE is returned
  *            after the steps, with rho unspecified.
  *   stats  : host, may be NULL.
- * On PCMCC_ECAPACITY the arrays hold the state after stats->steps_done
- * committed steps and the deposit is skipped.  Synchronises the stream. */
+ * A step is committed when its survivors fit p->capacity (where they do so
+ * only in the slots of electrons that the same step removes, each newborn
+ * generation must also fit half the capacity).  On PCMCC_ECAPACITY the arrays
+ * hold the state after stats->steps_done committed steps and the deposit is
+ * skipped; slots beyond the count may have been written.  Synchronises the
+ * stream. */
 int pcmcc_push_collide_deposit(pcmcc_ctx* ctx, const pcmcc_particles* p, const pcmcc_grid* field, double dt,
                                int n_steps, uint64_t seed, uint64_t step0, int64_t* rho, pcmcc_stats* stats);
 

@@ -88,7 +88,8 @@ int pcmcc_mlp_train(pcmcc_ctx* c, const float* params_in, int64_t n, const float
   int per_cu = 0;
   HIP_TRY(c, occupancy_mlp_train(&per_cu));
   if (per_cu < 1) return fail(c, PCMCC_EHIP, "training kernel does not fit on a compute unit");
-  const int nb = (int)std::min<int64_t>(std::min<int64_t>((n + kMlpTile - 1) / kMlpTile, (int64_t)per_cu * c->num_cu), 1024);
+  const int64_t tiles = (n + kMlpTile - 1) / kMlpTile;
+  const int nb = (int)std::min<int64_t>(std::min<int64_t>(tiles, (int64_t)per_cu * c->num_cu), 1024);
   MlpDev d;
   float inv_cnt = 0;
   int rc = mlp_upload(c, d, params_in, n, x, t, mask, std::max(nb, 1), &inv_cnt);

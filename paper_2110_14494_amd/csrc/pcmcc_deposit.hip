@@ -188,7 +188,8 @@ __device__ __forceinline__ uint2 table_count(TileTable<N>& H, uint32_t t, bool v
     }
     const uint32_t e = (uint32_t)__builtin_amdgcn_readlane((int)r.x, lead);
     const uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)r.y, lead);
-    r = make_uint2(e, b + __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u)));
+    const uint32_t below = __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u);
+    r = make_uint2(e, b + __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), below));
     valid = valid && !((same >> lane) & 1);
   }
   if (valid) {
@@ -569,8 +570,8 @@ hipError_t launch_deposit_binned(const float* x, const float* y, const float* z,
   hipLaunchKernelGGL(k_dep_scatter, dim3((unsigned)((n + kBinRange - 1) / kBinRange)), dim3(kBinThreads), 0, stream, x,
                      y, z, w, n, T, W.tile_count, W.sorted);
   const uint32_t range = acc_range(n);
-  hipLaunchKernelGGL(k_dep_accum, dim3((unsigned)((n + range - 1) / range)), dim3(256), 0, stream, W.sorted, n, range, T, W.tile_start,
-                     (unsigned long long*)rho);
+  hipLaunchKernelGGL(k_dep_accum, dim3((unsigned)((n + range - 1) / range)), dim3(256), 0, stream, W.sorted, n, range,
+                     T, W.tile_start, (unsigned long long*)rho);
   return hipGetLastError();
 }
 

@@ -573,7 +573,8 @@ __device__ void tail_direct(float* u, const float* f, MgDims d, float h2, double
   pass(w1, w0, my, ny, nx, true, keep);
   pass(w0, w1, mz, nz, nx * ny, true, [&](double* b, int c, double s) {
     const int i = c % nx, j = (c / nx) % ny, k = c / (nx * ny);
-    const double a = sinpi((double)i / (2 * nx)), e = sinpi((double)j / (2 * ny)), g = sinpi((double)(k + 1) / (2 * nz));
+    const double a = sinpi((double)i / (2 * nx)), e = sinpi((double)j / (2 * ny));
+    const double g = sinpi((double)(k + 1) / (2 * nz));
     b[c] = -s * (double)h2 / (4.0 * (a * a + e * e + g * g));
   });
   pass(w1, w0, mz, nz, nx * ny, false, keep);
@@ -649,16 +650,8 @@ __global__ __launch_bounds__(kTailThreads) void k_mg_tail(MgTailArgs A) {
   for (int c = threadIdx.x; c < n0; c += kTailThreads) A.u[c] = s_u[c];
 }
 
-// Defect of the potential, r = rhs - L phi in double precision: stored in
-// single precision as the right-hand side of the correction cycle; a block's
-// largest magnitude goes to part[block] (k_max_parts reduces them:
-// one same-address atomic per block would serialise in the memory-side
-// atomic unit).  A thread takes a pair of cells of a row, one of each colour:
-// pairs load as 16 bytes and the lanes of a wave read consecutive ones (108 ->
-// 84 us at 256^3 with 268 MB to read; four pairs a thread leave 64-byte strides
-// between the lanes, 112 us).
-// kAligned: the caller's potential lies on 16 bytes, so that pairs of cells of
-// a row (nx is even) load as one; it need not.
+// Two consecutive cells of a row (nx is even).  kAligned: the caller's potential
+// lies on 16 bytes, so that they load as one; it need not.
 template <bool kAligned>
 __device__ __forceinline__ void load_2(const double* p, double& a, double& b) {
   if constexpr (kAligned) {
@@ -671,6 +664,7 @@ __device__ __forceinline__ void load_2(const double* p, double& a, double& b) {
   }
 }
 
+// The block's largest |defect| to its entry of part.
 __device__ __forceinline__ void defect_max(double m, double* part) {
   __shared__ double s_w[kMgThreads / 64];
   m = wave_max(m);
@@ -682,6 +676,14 @@ __device__ __forceinline__ void defect_max(double m, double* part) {
   }
 }
 
+// Defect of the potential, r = rhs - L phi in double precision: stored in
+// single precision as the right-hand side of the correction cycle; a block's
+// largest magnitude goes to part[block] (k_max_parts reduces them:
+// one same-address atomic per block would serialise in the memory-side
+// atomic unit).  A thread takes a pair of cells of a row, one of each colour:
+// pairs load as 16 bytes and the lanes of a wave read consecutive ones (108 ->
+// 84 us at 256^3 with 268 MB to read; four pairs a thread leave 64-byte strides
+// between the lanes, 112 us).
 template <bool kAligned>
 __global__ __launch_bounds__(kMgThreads) void k_mg_defect(const double* __restrict__ phi,
                                                           const double* __restrict__ rhs, int nx, int ny, int nz,

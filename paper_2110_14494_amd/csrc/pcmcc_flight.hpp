@@ -512,10 +512,10 @@ __device__ __forceinline__ uint32_t wave_place() {
 // (tables of ROW floats per node, table_row(nproc)),
 // REFILL lanes at a time (see above), `chunk` (a power of two in [kChunkMin,
 // kChunkMax], read from the kernel arguments) electrons per work-counter
-// grab at most, and less as the work runs out.  A wave's first chunk is its own by position (no atomic): with the work
-// counter's same-address atomics, 13 ns each, 4096 waves would need 55 us
-// just to find out what there is to do, which is all that a newborn
-// generation of a few thousand electrons takes.
+// grab at most, and less as the work runs out.  A wave's first chunk is its own
+// by position (no atomic): with the work counter's same-address atomics, 13 ns
+// each, 4096 waves would need 55 us just to find out what there is to do, which
+// is all that a newborn generation of a few thousand electrons takes.
 // Field: key(tag) gives the random-number key of a group, accel(x, y, z,
 // tag, where) the acceleration (and where the field was read), bound_at(where,
 // tag, speed, t_rem, a_abs, da) the field bounds for the rest of the step.
@@ -528,14 +528,18 @@ __device__ __forceinline__ uint32_t wave_place() {
 // (it may flush on its own), flush(WaveStage*, count) writes out the wave's
 // staged results; can_open() tells whether the wave may take another chunk
 // of work, open_chunk(first, size) registers a chunk it took and returns its
-// tag, which tag(Flight&, tag) gives each electron loaded from it.  Must be called by whole waves with wave-uniform
-// arguments; `take` is the grid-wide work counter beyond the first chunks
-// (zero before the first wave starts).  cum_ion (nullable) counts ionizations per group.  Every
-// staged entry is written out before the function returns.
-// place(): the wave's among all of the grid (wave_place).
+// tag, which tag(Flight&, tag) gives each electron loaded from it.  Must be
+// called by whole waves with wave-uniform arguments; `take` is the grid-wide
+// work counter beyond the first chunks (zero before the first wave starts).
+// cum_ion (nullable) counts ionizations per group.  Every staged entry is
+// written out before the function returns.
+// place(): the wave's among all of the grid (wave_place).  local: the wave runs
+// its own newborns, up to `quota` of them (newborn_quota); otherwise all go to
+// the queue.
 template <int REFILL, int ROW, class Place, class Field, class Source, class Finish>
-__device__ __forceinline__ void fly_all(bool local, uint32_t quota, const Place& place, uint64_t n, unsigned long long* take, KArg<uint32_t> chunk, double dt,
-                                        const Field& F, const Tab& T, const SpeciesView& S, uint32_t step, Cnt& cnt,
+__device__ __forceinline__ void fly_all(bool local, uint32_t quota, const Place& place, uint64_t n,
+                                        unsigned long long* take, KArg<uint32_t> chunk, double dt, const Field& F,
+                                        const Tab& T, const SpeciesView& S, uint32_t step, Cnt& cnt,
                                         const BirthSink& sink, unsigned long long* cum_ion, WaveStage* L,
                                         const Source& source, const Finish& finish) {
   Flight f;

@@ -9,8 +9,9 @@
 // 512 blocks of 8 waves), and a commit by one block needs a second barrier.
 // Here the last block to arrive runs a completion function on its own while
 // the others wait, and publishes what it returns in the words the others
-// are waiting for: one barrier costs about 3 us in all, the numbers
-// included.
+// are waiting for: one barrier costs 5.6 us over 256 blocks and 9.5 us over
+// 512 (of 256 or 512 threads, one after the other without work between them),
+// the numbers included.
 //
 // Arrivals are counted in kBarGroups counters on cache lines of their own
 // (a same-address atomic takes about 13 ns on this device, 6.6 us for 512

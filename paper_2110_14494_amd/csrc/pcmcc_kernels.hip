@@ -16,9 +16,10 @@
 // stay within that chunk's slot range of the next buffer (ping-pong, so a
 // step that would overflow the capacity leaves the previous state intact),
 // written to its front in the order they finish; the rest of the range is
-// holes that the step's newborns fill first, and any holes left over are
-// filled from the tail.  Only newborns and holes take global atomics, one
-// per wave and batch.
+// holes.  Newborns append behind the population, the last of them are then
+// moved into the holes, and holes left over are filled from the tail (a step
+// that does not fit this way runs again with its newborns going into the holes
+// first).  Only newborns and holes take global atomics, one per wave and batch.
 #include <hip/hip_runtime.h>
 
 #include "pcmcc_device.hpp"
@@ -152,7 +153,7 @@ struct PlaceNewborn {
 // entry.  Writing each chunk's survivors consecutively keeps a few partly
 // written lines per chunk open in the cache instead of one per survivor.
 struct ChunkRing {
-  static constexpr uint32_t kR = 64;  // more than the 64 lanes can keep open, plus the chunk being loaded
+  static constexpr uint32_t kR = 64;  // the chunks of a wave's 64 lanes; with all open it waits (can_open)
   uint64_t base[kR];
   uint32_t size[kR], cursor[kR], remaining[kR];
   uint32_t head;
@@ -413,23 +414,24 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
     {
       const BirthSink sink{{&ka->pend[0]}, &ctl->pend[0].v, A.pend_cap, &ctl->overflow.v, 0u, ev_k};
       const SoaSource src{cur_k};
-      const KeepInPlace fin{grid_k, nxt_k, A.holes, &ctl->holes.v, ev_k, ring,
-                            PlaceNewborn{grid_k, nxt_k, A.holes, 0, n_cur, A.cap, &ctl->child.v, &ctl->overflow.v, ev_k}};
+      const PlaceNewborn born{grid_k, nxt_k, A.holes, 0, n_cur, A.cap, &ctl->child.v, &ctl->overflow.v, ev_k};
+      const KeepInPlace fin{grid_k, nxt_k, A.holes, &ctl->holes.v, ev_k, ring, born};
       ring->reset();
-      fly_all<REFILL, ROW>(local, quota, place, n_cur, &ctl->take[0].v, chunk_k, A.dt, F, T, A.S, step, cnt, sink, nullptr, L, src,
-                                 fin);
+      fly_all<REFILL, ROW>(local, quota, place, n_cur, &ctl->take[0].v, chunk_k, A.dt, F, T, A.S, step, cnt, sink,
+                           nullptr, L, src, fin);
     }
     grid_barrier(&ctl->bar, gen, s_pub, [&](uint32_t* v) { step_advance(A, v, 0, n_cur, local); });
 
-    // Phase 2: newborns, one generation at a time.  Survivors fill the holes
-    // first, then append after the current count.
+    // Phase 2: newborns that went to the queue, one generation at a time.
+    // Survivors append after the current count, or, in a step that is run
+    // again, fill the holes first.
     for (int g = 0; word(0) == STEP_NEWBORN; ++g) {
       const uint32_t np = word(1), h = local ? 0u : word(2);
       const BirthSink sink{{&ka->pend[(g + 1) & 1]}, &ctl->pend[(g + 1) & 1].v, A.pend_cap, &ctl->overflow.v, 0u, ev_k};
       const PendSource src{{&ka->pend[g & 1]}, kSrcBorn + 1u + (uint32_t)g};
       const PlaceNewborn fin{grid_k, nxt_k, A.holes, h, n_cur, A.cap, &ctl->child.v, &ctl->overflow.v, ev_k};
-      fly_all<REFILL, ROW>(local, quota, place, np, &ctl->take[(g + 1) & 1].v, chunk_k, A.dt, F, T, A.S, step, cnt, sink, nullptr, L,
-                                 src, fin);
+      fly_all<REFILL, ROW>(local, quota, place, np, &ctl->take[(g + 1) & 1].v, chunk_k, A.dt, F, T, A.S, step, cnt,
+                           sink, nullptr, L, src, fin);
       grid_barrier(&ctl->bar, gen, s_pub, [&](uint32_t* v) { step_advance(A, v, g + 1, n_cur, local); });
     }
 

@@ -318,8 +318,8 @@ __global__ __launch_bounds__(256) void k_mlp_reduce(const float* __restrict__ pa
 
 // Every epoch: gradient (all blocks), fixed-order reduction and Adam update
 // (the parameters dealt over the blocks), then the blocks reload the
-// parameters.  Two grid barriers per epoch; the barrier's completion sums the
-// loss.
+// parameters.  Two grid barriers per epoch; the last block, which has the
+// fewest parameters, sums the loss.
 __global__ __launch_bounds__(256) void k_mlp_train(MlpArgs A) {
   __shared__ MlpLds L;
   __shared__ uint32_t s_pub[kBarWords];

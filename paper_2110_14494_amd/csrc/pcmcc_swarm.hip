@@ -9,8 +9,9 @@
 // over all swarms' electrons at once, the swarm index being the electron's
 // group (its field, its random-number key, its destination region); survivors
 // are appended to region s of the next buffer, one atomic per swarm and
-// batch.  Newborns of all swarms share one queue that carries the swarm
-// index.  Population control runs when an electron is loaded in the next
+// batch.  A wave runs its own newborns; duplicates, and newborns that find no
+// place in the wave's list, go through one queue for all swarms that carries the
+// swarm index.  Population control runs when an electron is loaded in the next
 // step (keep with probability 2^-k, or duplicate).  Moments are summed
 // exactly in 128-bit fixed point, so they do not depend on the order in
 // which particles land in the buffers.
@@ -49,7 +50,7 @@ struct SwarmField {
   }
 };
 
-// Swarm of global electron index g: the last s with prefix[s] <= g.
+// Swarm of global electron (or tile) index g: the last s with prefix[s] <= g.
 __device__ __forceinline__ int swarm_of(const uint32_t* prefix, int S, uint32_t g);
 
 // Phase 1 source: the electrons of all swarms (prefix of counts in LDS),
@@ -249,24 +250,6 @@ __device__ __forceinline__ int swarm_of(const uint32_t* prefix, int S, uint32_t 
   return lo;
 }
 
-// Swarm owning tile tt: the last s with prefix[s] <= tt.
-__device__ __forceinline__ int find_swarm(const uint32_t* prefix, int S, uint32_t tt) {
-  int lo = 0, hi = S;  // prefix[lo] <= tt < prefix[hi]
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (prefix[mid] <= tt)
-      lo = mid;
-    else
-      hi = mid;
-  }
-  return lo;
-}
-
-__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-  return v;
-}
-
 // ---------------------------------------------------------------------------
 // The step loop: phases, barriers and counters as in the PIC step's
 // (grid_barrier; a step without a sample and without newborns has one
@@ -383,8 +366,8 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) void k_
     {
       const BirthSink sink{{&ka->pend[0]}, &ctl->pend[0].v, A.pend_cap, &ctl->overflow.v, 0u, no_events};
       const SwarmLoad src{cur_k, base_l, prefix, pck, S, A.key, step, sink, &psteps};
-      fly_all<REFILL, ROW>(true, quota, wave_place, (uint64_t)prefix[S], &ctl->take[0].v, chunk_k, (double)A.dt, F, T, A.S, step, cnt, sink,
-                      A.cum_ion, L, src, fin);
+      fly_all<REFILL, ROW>(true, quota, wave_place, (uint64_t)prefix[S], &ctl->take[0].v, chunk_k, (double)A.dt, F, T,
+                           A.S, step, cnt, sink, A.cum_ion, L, src, fin);
     }
     grid_barrier(&ctl->bar, gen, s_pub, [&](uint32_t* v) { swarm_advance(A, v, 0, sample); });
 
@@ -394,8 +377,8 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) void k_
       const BirthSink sink{{&ka->pend[(g + 1) & 1]}, &ctl->pend[(g + 1) & 1].v, A.pend_cap, &ctl->overflow.v, 0u,
                            no_events};
       const SwarmPend src{{&ka->pend[g & 1]}};
-      fly_all<REFILL, ROW>(true, quota, wave_place, np, &ctl->take[(g + 1) & 1].v, chunk_k, (double)A.dt, F, T, A.S, step, cnt, sink,
-                                  A.cum_ion, L, src, fin);
+      fly_all<REFILL, ROW>(true, quota, wave_place, np, &ctl->take[(g + 1) & 1].v, chunk_k, (double)A.dt, F, T, A.S,
+                           step, cnt, sink, A.cum_ion, L, src, fin);
       grid_barrier(&ctl->bar, gen, s_pub, [&](uint32_t* v) { swarm_advance(A, v, g + 1, sample); });
     }
 
@@ -422,7 +405,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) void k_
       }
       __syncthreads();
       for (uint32_t tt = t0; tt < t1; ++tt) {
-        const int s = find_swarm(prefix, S, tt);
+        const int s = swarm_of(prefix, S, tt);
         if (s != cur_s) {
           if (cur_s >= 0 && threadIdx.x < kNMom) {
             unsigned long long* dst = A.mom + (((size_t)cur_s * A.n_samples + j) * kNMom + threadIdx.x) * 2;

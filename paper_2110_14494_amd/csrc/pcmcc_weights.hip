@@ -181,8 +181,9 @@ __global__ void k_wt_heads(const uint64_t* __restrict__ key2, uint64_t m, uint32
 // per candidate, a weight and a class written per pair (758 us with the weight
 // and the id read from the particles' arrays, 552 us so, for 2^24 particles).
 __global__ void k_wt_pair(const uint64_t* __restrict__ key2, const uint32_t* __restrict__ slot,
-                          const WeightCand* __restrict__ cand, const uint32_t* __restrict__ run_start, uint64_t m, Soa cur, uint8_t* __restrict__ cls,
-                          Key key, uint32_t update_index, unsigned long long* n_pairs) {
+                          const WeightCand* __restrict__ cand, const uint32_t* __restrict__ run_start, uint64_t m,
+                          Soa cur, uint8_t* __restrict__ cls, Key key, uint32_t update_index,
+                          unsigned long long* n_pairs) {
   unsigned long long pairs = 0;  // the wave's pairs, counted by lane 0
   for (uint64_t base = (uint64_t)blockIdx.x * blockDim.x; base < m; base += (uint64_t)gridDim.x * blockDim.x) {
     const uint64_t k = base + threadIdx.x;
