@@ -58,7 +58,7 @@ SLOTS_BIRTH = 150.0      # a newborn: its Philox draw, direction and speed
 SLOTS_PSTEP = 35.0       # a particle-step: start (conversions, field bound) and finish (domain test, stores)
 BYTES_PER_PSTEP = 72.0  # 36 B read + 36 B written
 BYTES_PER_BIRTH = 36.0  # the newborn written
-BYTES_QUEUE_PER_BIRTH = 80.0  # the newborn queue's own round trip (40 B written, 40 B read back), reported apart
+BYTES_QUEUE_PER_BIRTH = 0.0  # a wave runs its own newborns: no round trip through the queue (reported apart)
 KERNEL_SOURCES = ("paper_2110_14494_amd/csrc/pcmcc_kernels.hip", "paper_2110_14494_amd/csrc/pcmcc_flight.hpp",
                   "paper_2110_14494_amd/csrc/pcmcc_mover.hpp", "paper_2110_14494_amd/csrc/pcmcc_device.hpp",
                   "paper_2110_14494_amd/csrc/pcmcc_internal.hpp", "paper_2110_14494_amd/csrc/pcmcc_runtime.hip")
