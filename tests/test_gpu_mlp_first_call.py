@@ -1,7 +1,8 @@
 """A context's first surrogate evaluation takes no memory of its own: it may
 cost little more than the next one.  An allocation on the device and one of
 pinned host memory on that call cost some 28 us, either alone 10 us or more;
-the medians over 25 contexts may differ by 10 us.  Descriptions of growing
+the least times of 25 contexts (other work on the machine only adds) may differ
+by 10 us.  Descriptions of growing
 and shrinking size in one context give what a fresh context gives."""
 import time
 
@@ -44,7 +45,7 @@ def test_first_call_of_a_context(inputs):
                 t.append(time.perf_counter())
         first.append(t[1] - t[0])
         second.append(t[2] - t[1])
-    a, b = (1e6 * float(np.median(v[1:])) for v in (first, second))  # (the first loads the kernel)
+    a, b = (1e6 * min(v[1:]) for v in (first, second))  # (the first context loads the kernel)
     print(f"[gpu] first {a:.1f} us, second {b:.1f} us", flush=True)
     assert a <= b + 10.0
 

@@ -40,6 +40,7 @@ def test_a_runaway_step_ends_at_its_first_overflow():
     is well below that."""
     rc, _, _, st, _, _ = _run(20.0, 4, np.array([2000, 20000], dtype=np.int32))
     assert rc == -2 and st["steps_done"] == 0
+    print(f"[gpu] runaway swarm step {st['step_kernel_ms']:.2f} ms", flush=True)
     assert st["step_kernel_ms"] < 250.0, st["step_kernel_ms"]
 
 
@@ -81,6 +82,7 @@ def test_the_particle_step_likewise(growth, room, rc_want):
             dp = pic.Particles.from_numpy(parts, room * n)
             rc, st = ctx.push_collide_deposit(dp, pic.DeviceGrid(grid), growth * 1e-12, 1, 5, check=False)
             g = dp.to_numpy()
+        print(f"[gpu] growth e^{growth:g} {st['step_kernel_ms']:.2f} ms", flush=True)
         assert rc == rc_want and st["step_kernel_ms"] < 250.0, (rc, st["step_kernel_ms"])
         if rc_want == 0:
             orc, o, ost = oracle.pic_run(sp, tab, grid, parts, growth * 1e-12, 1, 5, capacity=room * n)

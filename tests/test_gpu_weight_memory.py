@@ -22,6 +22,7 @@ def test_memory_of_a_contexts_first_update(pic):  # noqa: F811
         before = torch.cuda.mem_get_info()[0]
         rc, _ = ctx.update_weights(dp, dg, 1000.0, 1, 0, check=False)
         taken = before - torch.cuda.mem_get_info()[0]
+    print(f"[gpu] first update took {taken / n:.1f} B a particle", flush=True)
     assert rc == 0
     sort = 12  # B a particle
     # two per cent for the sort's counters, 2 MiB for each of the ten allocations
